@@ -1,12 +1,14 @@
 // Periodic retarded-time shell kernel G_k (Eq. 10, algorithm step 2) and the
 // folding of its FP64 spectrum (step 3), plus small utility kernels.
 //
-// Builder: one thread per cell of the non-negative octant c in [0, N/2]^3.
-// For every periodic image u whose cell box can reach [r_k, r_{k+1}) it sums
-// the m^3 subpoints with exact integer squared distance n (units of the
-// half-subcell h = L/(2 m N)) inside [T_k, T_{k+1}), each weighing
-// pref * phi(rho) / (4 pi rho^2) / m^3, rho = sqrt(n) h. G is even in every
-// axis, so the octant value is written to all of its mirror cells.
+// Builder: the cells of the non-negative octant c in [0, N/2]^3, a batch of
+// consecutive shells per launch. For every periodic image u whose cell box
+// can reach the batch's shells the m^3 subpoints are summed, each into the
+// shell whose [T_k, T_{k+1}) holds its exact integer squared distance n
+// (units of the half-subcell h = L/(2 m N)), weighing
+// pref * phi(rho) / (4 pi rho^2) / m^3, rho = sqrt(n) h. G is real and even in
+// every axis, so its spectrum is the cosine transform of the octant along
+// each axis (lc_dct.hip): no mirrored grid and no complex spectrum is formed.
 #include <algorithm>
 
 #include "lc_fft_device.h"
@@ -64,7 +66,7 @@ __device__ double circle_in_rect(double R, double x0, double x1, double y0, doub
     return arc_quarter(R, x0, y0) - arc_quarter(R, x1, y0) - arc_quarter(R, x0, y1) + arc_quarter(R, x1, y1);
 }
 
-__device__ double exact_v(const ExactRule &e, double R, double z0, double z1) {
+__device__ double exact_v(const ExactShell &e, const GaussRule &g, double R, double z0, double z1) {
     if (!(R < e.r_sup)) return 0.0;
     const double wH = acosh(e.r_sup / R), wL = R < e.r_lo ? acosh(e.r_lo / R) : 0.0;
     const double wa = asinh(z0 / R), wb = asinh(z1 / R);
@@ -86,10 +88,10 @@ __device__ double exact_v(const ExactRule &e, double R, double z0, double z1) {
             const double w0 = lo + q * len;
             double sq = 0.0;
             for (int j = 0; j < 16; ++j) {
-                const double w = w0 + len * e.gx[j], ch = cosh(w), r = R * ch;
+                const double w = w0 + len * g.x[j], ch = cosh(w), r = R * ch;
                 const double v = e.a * exp(-pow(r / e.s, e.p)) - e.c;
                 const double ph = (e.kind == 1 && v < 0.0) ? 0.0 : v;   // (kind 2: r < r_sup <= cut)
-                sq += e.gw[j] * ph / ch;
+                sq += g.w[j] * ph / ch;
             }
             acc += len * sq;
         }
@@ -97,7 +99,8 @@ __device__ double exact_v(const ExactRule &e, double R, double z0, double z1) {
     return acc;
 }
 
-__device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0, double y1, double z0, double z1) {
+__device__ double cell_exact(const ExactShell &e, const GaussRule &g, double x0, double x1, double y0, double y1, double z0,
+                             double z1) {
     if (!(e.r_sup > e.r_lo)) return 0.0;
     const double nx = x0 > 0.0 ? x0 : (x1 < 0.0 ? -x1 : 0.0);
     const double ny = y0 > 0.0 ? y0 : (y1 < 0.0 ? -y1 : 0.0);
@@ -134,10 +137,10 @@ __device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0
         const double pi = 3.141592653589793238;
         double sq = 0.0;
         for (int j = 0; j < 16; ++j) {
-            const double u = pi * e.gx[j];
+            const double u = pi * g.x[j];
             const double R = lo + 0.5 * (hi - lo) * (1.0 - cos(u));
             const double jac = pi * 0.5 * (hi - lo) * sin(u);
-            sq += e.gw[j] * jac * circle_in_rect(R, x0, x1, y0, y1) * exact_v(e, R, z0, z1);
+            sq += g.w[j] * jac * circle_in_rect(R, x0, x1, y0, y1) * exact_v(e, g, R, z0, z1);
         }
         return sq;
     };
@@ -149,7 +152,7 @@ __device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0
         if (Ra == 0.0 && source_cell) {
             // (the top piece keeps the substitution: R = Rb may be a square-root end)
             double hi = Rb;
-            for (int g = 0; g < 50; ++g) {
+            for (int i = 0; i < 50; ++i) {
                 acc += piece(0.5 * hi, hi);
                 hi *= 0.5;
             }
@@ -175,7 +178,7 @@ __device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0
                 if (dl < mid - lo) {
                     acc += piece(lo, lo + dl);
                     lo += dl;
-                    for (int g = 0; g < 64 && lo - Ra < mid - lo; ++g) {
+                    for (int i = 0; i < 64 && lo - Ra < mid - lo; ++i) {
                         const double d = lo - Ra;
                         acc += piece(lo, lo + d);
                         lo += d;
@@ -186,7 +189,7 @@ __device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0
                 if (dr < hi - mid) {
                     acc += piece(hi - dr, hi);
                     hi -= dr;
-                    for (int g = 0; g < 64 && Rb - hi < hi - mid; ++g) {
+                    for (int i = 0; i < 64 && Rb - hi < hi - mid; ++i) {
                         const double d = Rb - hi;
                         acc += piece(hi - d, hi);
                         hi -= d;
@@ -201,141 +204,145 @@ __device__ double cell_exact(const ExactRule &e, double x0, double x1, double y0
     return e.pref * acc / (four_pi * e.l * e.l * e.l);
 }
 
-__global__ __launch_bounds__(256) void greens_build_kernel(BuildArgs a) {
+// Shells of a batch, all at once. A group of LPC lanes takes one octant cell:
+// the images that can reach the batch are found once per cell (a few; the
+// ranges of u are computed, not searched), and each subpoint's shell from its
+// exact squared distance, so the radial factor is evaluated once per subpoint
+// however many shells the batch holds. Arithmetic bound (FP64 pow, exp and
+// sqrt per subpoint). One launch per shell, every cell testing every image,
+// took 220 us a shell at 128^3 (24 shells, m = 4); the batches take 11.6 us.
+// The group adds to G[k][cell] itself, which no other group touches: no
+// atomics, and the result does not depend on timing. LPC = 8 spreads the m^3
+// subpoints of a cell over eight lanes (m = 1 has one, the exact rule works
+// cell by cell: LPC = 1).
+template <int LPC, bool EXACT>
+__global__ __launch_bounds__(256) void greens_shells_kernel(ShellArgs a) {
+    constexpr int KM = ShellArgs::kMax;
+    // (three more edges, equal to the last: empty shells past the batch's end)
+    __shared__ double T[KM + 4], r[KM + 4];
+    __shared__ ExactShell sh[KM];
+    __shared__ double cut[KM];
+    __shared__ GaussRule rule16;
+    const int cnt = a.count;
+    if (threadIdx.x < KM + 4) {
+        const int i = (int)threadIdx.x < cnt ? (int)threadIdx.x : cnt;
+        T[threadIdx.x] = a.T[i];
+        r[threadIdx.x] = a.r[i];
+    }
+    if ((int)threadIdx.x < cnt) {
+        sh[threadIdx.x] = a.sh[threadIdx.x];
+        cut[threadIdx.x] = a.cut[threadIdx.x];
+    }
+    if (EXACT && threadIdx.x < 16) {
+        rule16.x[threadIdx.x] = a.rule16.x[threadIdx.x];
+        rule16.w[threadIdx.x] = a.rule16.w[threadIdx.x];
+    }
+    __syncthreads();
     const int n = a.n, H = n / 2 + 1;
-    const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (cell >= (int64_t)H * H * H) return;
+    const int64_t cells = (int64_t)H * H * H;
+    const int64_t cell = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPC;
+    const int sub = threadIdx.x % LPC;
+    if (cell >= cells) return;   // (a whole group leaves together)
     const int ci = (int)(cell / ((int64_t)H * H)), cj = (int)((cell / H) % H), ck = (int)(cell % H);
-    const int m = a.m, U = a.images;
-    const double l = a.l;
+    double *__restrict__ G = a.oct + cell;
+    const int m = a.m, m3 = m * m * m;
+    const double l = a.l, r_lo = r[0], r_hi = r[cnt];
     const double four_pi = 12.566370614359172954;
-    const double wm = a.pref / ((double)m * m * m);
-    const double margin = 1e-9 * (a.r_hi + l);
-    double acc = 0.0;
-    for (int u0 = -U; u0 <= U; ++u0) {
-        const int64_t x0 = ci + (int64_t)u0 * n;
-        const double lo0 = (x0 - 0.5) * l, hi0 = (x0 + 0.5) * l;
-        const double nr0 = lo0 > 0 ? lo0 : (hi0 < 0 ? -hi0 : 0.0), fr0 = fmax(fabs(lo0), fabs(hi0));
-        for (int u1 = -U; u1 <= U; ++u1) {
-            const int64_t x1 = cj + (int64_t)u1 * n;
-            const double lo1 = (x1 - 0.5) * l, hi1 = (x1 + 0.5) * l;
-            const double nr1 = lo1 > 0 ? lo1 : (hi1 < 0 ? -hi1 : 0.0), fr1 = fmax(fabs(lo1), fabs(hi1));
-            for (int u2 = -U; u2 <= U; ++u2) {
-                const int64_t x2 = ck + (int64_t)u2 * n;
-                const double lo2 = (x2 - 0.5) * l, hi2 = (x2 + 0.5) * l;
-                const double nr2 = lo2 > 0 ? lo2 : (hi2 < 0 ? -hi2 : 0.0), fr2 = fmax(fabs(lo2), fabs(hi2));
+    const double margin = 1e-9 * (r_hi + l);
+    // |c + u n| <= reach, in cells, for every image that meets the batch
+    const int reach = (int)ceil(r_hi / l + 1.5);
+    auto u_first = [&](int c) { return -((reach + c) / n); };
+    auto u_last = [&](int c) { return reach >= c ? (reach - c) / n : -1; };
+    auto axis = [&](int x, double &lo, double &hi, double &nr, double &fr) {
+        lo = (x - 0.5) * l;
+        hi = (x + 0.5) * l;
+        nr = lo > 0 ? lo : (hi < 0 ? -hi : 0.0);
+        fr = fmax(fabs(lo), fabs(hi));
+    };
+    for (int u0 = u_first(ci); u0 <= u_last(ci); ++u0) {
+        const int x0 = ci + u0 * n;
+        double lo0, hi0, nr0, fr0;
+        axis(x0, lo0, hi0, nr0, fr0);
+        for (int u1 = u_first(cj); u1 <= u_last(cj); ++u1) {
+            const int x1 = cj + u1 * n;
+            double lo1, hi1, nr1, fr1;
+            axis(x1, lo1, hi1, nr1, fr1);
+            for (int u2 = u_first(ck); u2 <= u_last(ck); ++u2) {
+                const int x2 = ck + u2 * n;
+                double lo2, hi2, nr2, fr2;
+                axis(x2, lo2, hi2, nr2, fr2);
                 const double dmin = sqrt(nr0 * nr0 + nr1 * nr1 + nr2 * nr2);
                 const double dmax = sqrt(fr0 * fr0 + fr1 * fr1 + fr2 * fr2);
-                if (dmin > a.r_hi + margin || dmax < a.r_lo - margin) continue;
-                if (a.rule == 1) {
-                    acc += cell_exact(a.ex, lo0, hi0, lo1, hi1, lo2, hi2);
-                    continue;
+                if (dmin > r_hi + margin || dmax < r_lo - margin) continue;
+                // shells ka .. kb of the batch that this image cell can meet
+                int ka = 0, kb = cnt - 1;
+                while (ka < kb) {
+                    const int mid = (ka + kb) / 2;
+                    if (r[mid + 1] + margin < dmin) ka = mid + 1;
+                    else kb = mid;
                 }
-                if (a.self_pair && x0 == 0 && x1 == 0 && x2 == 0) {
-                    acc += a.self_val;     // zero unless this is slice 0
-                    continue;
-                }
-                for (int a0 = 0; a0 < m; ++a0) {
-                    const int64_t q0 = 2 * m * x0 + (2 * a0 + 1 - m);
-                    for (int a1 = 0; a1 < m; ++a1) {
-                        const int64_t q1 = 2 * m * x1 + (2 * a1 + 1 - m);
-                        const int64_t s01 = q0 * q0 + q1 * q1;
-                        for (int a2 = 0; a2 < m; ++a2) {
-                            const int64_t q2 = 2 * m * x2 + (2 * a2 + 1 - m);
-                            const int64_t nn = s01 + q2 * q2;
-                            const double dn = (double)nn;
-                            if (dn >= a.t_lo && dn < a.t_hi) {
+                while (kb + 1 < cnt && r[kb + 1] <= dmax + margin) ++kb;
+                if constexpr (EXACT) {
+                    for (int k = ka; k <= kb; ++k)
+                        if (sh[k].pref != 0.0) G[k * cells] += cell_exact(sh[k], rule16, lo0, hi0, lo1, hi1, lo2, hi2);
+                } else {
+                    if (a.self_pair && x0 == 0 && x1 == 0 && x2 == 0) {
+                        // the source's own cell belongs to slice 0
+                        if (a.has_first && sub == 0) G[0] += a.self_val;
+                        continue;
+                    }
+                    for (int kk = ka; kk <= kb; kk += 3) {
+                        const double t0 = T[kk], t1 = T[kk + 1], t2 = T[kk + 2], t3 = T[kk + 3];
+                        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
+                        for (int s = sub; s < m3; s += LPC) {
+                            const int a0 = s / (m * m), a1 = (s / m) % m, a2 = s % m;
+                            // (whole numbers below 2^53: exact in any order)
+                            const double q0 = 2.0 * m * x0 + (2 * a0 + 1 - m);
+                            const double q1 = 2.0 * m * x1 + (2 * a1 + 1 - m);
+                            const double q2 = 2.0 * m * x2 + (2 * a2 + 1 - m);
+                            const double dn = q0 * q0 + q1 * q1 + q2 * q2;
+                            if (dn >= t0 && dn < t3) {
+                                const int j = (dn >= t1 ? 1 : 0) + (dn >= t2 ? 1 : 0);
+                                const ExactShell &f = sh[kk + j];
                                 const double rho = sqrt(dn) * a.h;
-                                acc += wm * phi_eval(a.kind, rho, a.a, a.s, a.p, a.c, a.cut) /
-                                       (four_pi * rho * rho);
+                                const double v = f.pref / (double)m3 *
+                                                 phi_eval(f.kind, rho, f.a, f.s, f.p, f.c, cut[kk + j]) /
+                                                 (four_pi * rho * rho);
+                                acc0 += j == 0 ? v : 0.0;
+                                acc1 += j == 1 ? v : 0.0;
+                                acc2 += j == 2 ? v : 0.0;
                             }
+                        }
+#pragma unroll
+                        for (int o = LPC / 2; o > 0; o >>= 1) {
+                            acc0 += __shfl_xor(acc0, o, 64);
+                            acc1 += __shfl_xor(acc1, o, 64);
+                            acc2 += __shfl_xor(acc2, o, 64);
+                        }
+                        if (sub == 0) {
+                            if (acc0 != 0.0) G[kk * cells] += acc0;
+                            if (acc1 != 0.0) G[(kk + 1) * cells] += acc1;
+                            if (acc2 != 0.0) G[(kk + 2) * cells] += acc2;
                         }
                     }
                 }
             }
         }
     }
-    // mirror into the full grid
-    const int is[2] = {ci, (n - ci) % n}, js[2] = {cj, (n - cj) % n}, ks[2] = {ck, (n - ck) % n};
-    for (int a0 = 0; a0 < 2; ++a0)
-        for (int a1 = 0; a1 < 2; ++a1)
-            for (int a2 = 0; a2 < 2; ++a2)
-                a.grid[((int64_t)is[a0] * n + js[a1]) * n + ks[a2]] = acc;
 }
 
-hipError_t launch_greens_build(const BuildArgs &a, hipStream_t st) {
-    const int64_t H = a.n / 2 + 1;
-    const int64_t cells = H * H * H;
-    hipLaunchKernelGGL(greens_build_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// fold: FP64 spectrum -> real octant of the plan precision
-// ---------------------------------------------------------------------------
-template <typename TO>
-__global__ __launch_bounds__(256) void greens_fold_kernel(const cx<double> *__restrict__ spec, TO *__restrict__ oct,
-                                                          int n, int conserve, double target_over_l3,
-                                                          double *__restrict__ dc,
-                                                          unsigned long long *__restrict__ maxima) {
-    const int H = n / 2, HP = H + 1;
-    const int64_t total = (int64_t)HP * HP * HP;
-    const int64_t main_n = (int64_t)n * n * H;
-    const double g00 = spec[0].x;
-    const double f = conserve ? target_over_l3 / g00 : 1.0;
-    double mim = 0.0, mre = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(e / ((int64_t)HP * HP)), q = (int)((e / HP) % HP), p = (int)(e % HP);
-        cx<double> v;
-        int64_t o;
-        if (p < H) {
-            v = spec[((int64_t)r * n + q) * H + p];
-            o = ((int64_t)r * HP + q) * H + p;
-        } else {
-            v = spec[main_n + (int64_t)r * n + q];
-            o = (int64_t)HP * HP * H + (int64_t)r * HP + q;
-        }
-        oct[o] = (TO)(v.x * f);
-        mim = fmax(mim, fabs(v.y));
-        mre = fmax(mre, fabs(v.x));
-        if (e == 0) *dc = v.x * f;
-    }
-    __shared__ double red[2][4];
-    for (int o = 32; o > 0; o >>= 1) {
-        mim = fmax(mim, __shfl_down(mim, o, 64));
-        mre = fmax(mre, __shfl_down(mre, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = mim;
-        red[1][threadIdx.x >> 6] = mre;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) {
-            mim = fmax(mim, red[0][w]);
-            mre = fmax(mre, red[1][w]);
-        }
-        // non-negative doubles order like their bit patterns
-        atomicMax(&maxima[0], (unsigned long long)__double_as_longlong(mim));
-        atomicMax(&maxima[1], (unsigned long long)__double_as_longlong(mre));
-    }
-}
-
-hipError_t launch_greens_fold(int n, const void *spec64, void *oct, bool oct_f64, int conserve,
-                              double target_over_l3, double *dc, unsigned long long *maxima,
-                              hipStream_t st) {
-    const int64_t HP = n / 2 + 1;
-    const int64_t total = HP * HP * HP;
-    const int wgs = (int)std::min<int64_t>((total + 255) / 256, 1024);
-    if (oct_f64)
-        hipLaunchKernelGGL(greens_fold_kernel<double>, dim3(wgs), dim3(256), 0, st,
-                           (const cx<double> *)spec64, (double *)oct, n, conserve, target_over_l3, dc,
-                           maxima);
+hipError_t launch_greens_shells(const ShellArgs &a, hipStream_t st) {
+    if (a.count < 1 || a.count > ShellArgs::kMax || a.m < 1) return hipErrorInvalidValue;
+    const int64_t H = a.n / 2 + 1, cells = H * H * H;
+    hipError_t e = launch_fill_f64(a.oct, cells * a.count, 0.0, st);
+    if (e != hipSuccess) return e;
+    if (a.rule == 1)
+        hipLaunchKernelGGL((greens_shells_kernel<1, true>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, a);
+    else if (a.m == 1)
+        hipLaunchKernelGGL((greens_shells_kernel<1, false>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL(greens_fold_kernel<float>, dim3(wgs), dim3(256), 0, st,
-                           (const cx<double> *)spec64, (float *)oct, n, conserve, target_over_l3, dc,
-                           maxima);
+        hipLaunchKernelGGL((greens_shells_kernel<8, false>), dim3((unsigned)((cells * 8 + 255) / 256)), dim3(256), 0, st,
+                           a);
     return hipGetLastError();
 }
 
@@ -373,7 +380,7 @@ __global__ __launch_bounds__(256) void near_table_kernel(NearArgs a) {
     double acc = 0.0;
     if ((d0 | d1 | d2) && a.rule == 1) {
         const double l = a.l;
-        acc = cell_exact(a.ex, (d0 - 0.5) * l, (d0 + 0.5) * l, (d1 - 0.5) * l, (d1 + 0.5) * l, (d2 - 0.5) * l,
+        acc = cell_exact(a.ex, a.rule16, (d0 - 0.5) * l, (d0 + 0.5) * l, (d1 - 0.5) * l, (d1 + 0.5) * l, (d2 - 0.5) * l,
                          (d2 + 0.5) * l);
     } else if (d0 | d1 | d2) {
         for (int a0 = 0; a0 < m; ++a0) {

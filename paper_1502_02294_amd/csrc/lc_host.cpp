@@ -250,9 +250,8 @@ struct BoxPlan {
     bool spec3d = false;
     int xy_variant = 0;          // launch shape of the fused xy pass
     int push_group = 2;          // slices per batched forward launch in lc_step
-    unsigned long long *maxima = nullptr;
     char *tw_half = nullptr, *tw_full = nullptr, *twist = nullptr;       // plan precision
-    char *tw64_half = nullptr, *tw64_full = nullptr, *twist64 = nullptr; // FP64 (builder)
+    char *tw64_half = nullptr, *twist64 = nullptr;                       // FP64 (builder)
     int xwgs = 0;
     // FP32 form at N in {64, 96, 128, 192, 256}: x and y passes fused per plane
     bool use_xy = false;
@@ -272,7 +271,9 @@ struct lc_plan_s {
     int use_graph = 0;
     std::vector<BoxPlan> boxes;
     char *scratch_real = nullptr;    // FP64 N^3: builder grid / source staging / host-output staging
-    char *scratch_spec = nullptr;    // FP64 spectrum for the builder
+    char *scratch_spec = nullptr;    // staging spectrum of 3D pushes; follows scratch_real, and the
+                                     // builder's octants use both as one region
+    size_t scratch_bytes = 0;        // of that region
     // graph cache for lc_step
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
@@ -295,8 +296,8 @@ namespace {
 struct Layout {
     size_t total = 0;
     struct BoxOff {
-        size_t spec, acc, ghat, ghat0, dcpart, mu, sk, status, part, split_tab, maxima, tw_half, tw_full, twist,
-            tw64_half, tw64_full, twist64;
+        size_t spec, acc, ghat, ghat0, dcpart, mu, sk, status, part, split_tab, tw_half, tw_full, twist, tw64_half,
+            twist64;
     };
     std::vector<BoxOff> box;
     size_t scratch_real = 0, scratch_spec = 0;
@@ -369,12 +370,10 @@ Layout layout_of(const lc_plan_desc *d) {
         } else {
             o.part = o.split_tab = 0;
         }
-        o.maxima = take((size_t)B * 2 * 8);
         o.tw_half = take((size_t)(n / 2) * cs);
         o.tw_full = take((size_t)n * cs);
         o.twist = take((size_t)(n / 2) * cs);
         o.tw64_half = take((size_t)(n / 2) * 16);
-        o.tw64_full = take((size_t)n * 16);
         o.twist64 = take((size_t)(n / 2) * 16);
         lay.box.push_back(o);
         max_real = std::max(max_real, (size_t)n * n * n * 8);
@@ -672,6 +671,7 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
     p->use_graph = d->use_graph;
     p->scratch_real = p->ws + lay.scratch_real;
     p->scratch_spec = p->ws + lay.scratch_spec;
+    p->scratch_bytes = lay.total - lay.scratch_real;
     const size_t cs = p->t_f64 ? 16 : 8;
     for (int b = 0; b < d->n_boxes; ++b) {
         const lc_box_desc &x = d->boxes[b];
@@ -707,10 +707,8 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
             bp.fused_bands = std::min(x.n_bands, fused_max_bands(x.n));
             bp.fused_variant = fused_default_variant(x.n, bp.fused_bands);
         }
-        bp.maxima = (unsigned long long *)(p->ws + o.maxima);
         bp.tw_half = p->ws + o.tw_half; bp.tw_full = p->ws + o.tw_full; bp.twist = p->ws + o.twist;
-        bp.tw64_half = p->ws + o.tw64_half; bp.tw64_full = p->ws + o.tw64_full;
-        bp.twist64 = p->ws + o.twist64;
+        bp.tw64_half = p->ws + o.tw64_half; bp.twist64 = p->ws + o.twist64;
         bp.xwgs = x_pass_wgs(bp.n);
         bp.use_xy = p->prec == LC_PREC_FP32 && xy_supported(bp.n);
         bp.dcw = bp.dc_width();
@@ -722,7 +720,6 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
         twiddles64(n, n, tf.data());
         twiddles64(n, n / 2, tt.data());
         if ((rc = upload(bp.tw64_half, th.data(), (size_t)n / 2 * 16, p->stream))) return rc;
-        if ((rc = upload(bp.tw64_full, tf.data(), (size_t)n * 16, p->stream))) return rc;
         if ((rc = upload(bp.twist64, tt.data(), (size_t)n / 2 * 16, p->stream))) return rc;
         if (p->t_f64) {
             if ((rc = upload(bp.tw_half, th.data(), (size_t)n / 2 * 16, p->stream))) return rc;
@@ -819,63 +816,72 @@ int check_atten(const lc_atten *at, int k) {
 // Kernels of one (box, band), slice k with radial factor A[k] (algorithm
 // steps 2-3). Slices past the last one whose shell meets its factor's
 // support are skipped by the slice sum (kcount).
-// Shell k's constants for the exact cell average (kernel rule 1).
-ExactRule exact_rule(const BoxPlan &bp, const Atten &A, int k) {
-    ExactRule e;
+// Shell k's radial factor and the exact cell average's constants.
+ExactShell shell_of(const BoxPlan &bp, const Atten &A, int k) {
+    ExactShell e{};
     e.l = bp.l;
     e.r_lo = bp.radii[k];
     e.r_sup = std::min(bp.radii[k + 1], support_end(A));
     e.pref = A.pref;
     e.kind = A.kind;
     e.a = A.a; e.s = A.s; e.p = A.p; e.c = A.c;
+    return e;
+}
+
+GaussRule rule16() {
+    GaussRule g;
     std::vector<double> x, w;
     gauss01(16, x, w);
-    for (int j = 0; j < 16; ++j) { e.gx[j] = x[j]; e.gw[j] = w[j]; }
-    return e;
+    for (int j = 0; j < 16; ++j) { g.x[j] = x[j]; g.w[j] = w[j]; }
+    return g;
 }
 
 int build_impl(lc_plan_t *p, BoxPlan &bp, int band, const std::vector<Atten> &A) {
     const int n = bp.n, K = bp.K;
+    auto on = [&](int k) { return bp.radii[k] < support_end(A[k]) && A[k].pref != 0.0; };
     int kc = 0;
     for (int k = 0; k < K; ++k)
-        if (bp.radii[k] < support_end(A[k]) && A[k].pref != 0.0) kc = k + 1;
-    // the unit source's own cell belongs to slice 0 (r_0 = 0)
-    const double self = bp.radii[0] == 0.0 ? self_cell(A[0], bp.l) : 0.0;
+        if (on(k)) kc = k + 1;
     const double l3 = bp.l * bp.l * bp.l;
-    const int U = (int)std::ceil(bp.radii[K] / bp.L) + 1;
     const bool oct_f64 = p->t_f64;
     const size_t rs = oct_f64 ? 8 : 4;
     hipStream_t st = p->stream;
 
-    HIPCHK(launch_fill_bytes(bp.maxima + 2 * band, 16, st));
-    for (int k = 0; k < K; ++k) {
-        char *oct = bp.ghat + ((size_t)k * bp.B + band) * oct_elems(n) * rs;
-        double *dc = bp.ghat0 + (size_t)k * bp.B + band;
-        if (k >= kc || !(bp.radii[k] < support_end(A[k])) || A[k].pref == 0.0) {
-            HIPCHK(launch_fill_bytes(oct, oct_elems(n) * rs, st));
-            HIPCHK(launch_fill_f64(dc, 1, 0.0, st));
-            continue;
+    // slices in batches: as many FP64 octants as the plan's scratch holds (at
+    // least nine at every N), at most the shells one launch's arguments take
+    const int64_t H = n / 2 + 1, oe = H * H * H;
+    const int cap = (int)std::min<int64_t>(ShellArgs::kMax, (int64_t)p->scratch_bytes / (oe * 8));
+    double *oct64 = (double *)p->scratch_real;
+    ShellArgs a{};
+    a.oct = oct64;
+    a.n = n; a.m = bp.m; a.l = bp.l; a.h = bp.h;
+    a.rule = bp.rule;
+    // the unit source's own cell belongs to slice 0 (r_0 = 0)
+    a.self_pair = bp.radii[0] == 0.0 ? 1 : 0;
+    a.self_val = a.self_pair && on(0) ? self_cell(A[0], bp.l) : 0.0;
+    a.rule16 = rule16();
+    for (int k0 = 0; k0 < kc; k0 += cap) {
+        const int cnt = std::min(cap, kc - k0);
+        DctStore out{};
+        out.oct = bp.ghat; out.dc = bp.ghat0; out.g00 = bp.sk;
+        out.k0 = k0; out.B = bp.B; out.band = band; out.conserve = bp.conserve;
+        a.count = cnt;
+        a.has_first = k0 == 0;
+        for (int j = 0; j <= cnt; ++j) { a.r[j] = bp.radii[k0 + j]; a.T[j] = bp.T[k0 + j]; }
+        for (int j = 0; j < cnt; ++j) {
+            const int k = k0 + j;
+            a.sh[j] = shell_of(bp, A[k], k);
+            a.cut[j] = A[k].cut;
+            if (!on(k)) a.sh[j].pref = 0.0;   // (its cells stay zero)
+            out.target_over_l3[j] =
+                bp.conserve && on(k) ? (Phi(A[k], bp.radii[k + 1]) - Phi(A[k], bp.radii[k])) / l3 : -1.0;
         }
-        BuildArgs a;
-        a.grid = (double *)p->scratch_real;
-        a.n = n; a.m = bp.m; a.l = bp.l; a.h = bp.h;
-        a.t_lo = bp.T[k]; a.t_hi = bp.T[k + 1];
-        a.r_lo = bp.radii[k]; a.r_hi = bp.radii[k + 1];
-        a.images = U;
-        a.self_pair = bp.radii[0] == 0.0 ? 1 : 0;
-        a.self_val = (k == 0) ? self : 0.0;
-        a.kind = A[k].kind; a.a = A[k].a; a.s = A[k].s; a.p = A[k].p; a.c = A[k].c; a.cut = A[k].cut;
-        a.pref = A[k].pref;
-        a.rule = bp.rule;
-        a.ex = exact_rule(bp, A[k], k);
-        HIPCHK(launch_greens_build(a, st));
-        HIPCHK(launch_x_fwd(n, true, p->scratch_real, true, p->scratch_spec, bp.tw64_half, bp.twist64,
-                            nullptr, st));
-        HIPCHK(launch_col(n, true, 1, true, p->scratch_spec, bp.tw64_full, st));
-        HIPCHK(launch_col(n, true, 2, true, p->scratch_spec, bp.tw64_full, st));
-        const double target = bp.conserve ? (Phi(A[k], bp.radii[k + 1]) - Phi(A[k], bp.radii[k])) / l3 : 0.0;
-        HIPCHK(launch_greens_fold(n, p->scratch_spec, oct, oct_f64, bp.conserve, target, dc,
-                                  bp.maxima + 2 * band, st));
+        HIPCHK(launch_greens_shells(a, st));
+        HIPCHK(launch_greens_dct(n, oct64, cnt, bp.tw64_half, bp.twist64, out, oct_f64, st));
+    }
+    for (int k = kc; k < K; ++k) {
+        HIPCHK(launch_fill_bytes(bp.ghat + ((size_t)k * bp.B + band) * oct_elems(n) * rs, oct_elems(n) * rs, st));
+        HIPCHK(launch_fill_f64(bp.ghat0 + (size_t)k * bp.B + band, 1, 0.0, st));
     }
     bp.kcount[band] = kc;
     bp.built[band] = 1;
@@ -1223,6 +1229,7 @@ int lc_near_field(lc_plan_t *p, int32_t box, int32_t band, const lc_sources *src
     a.n = n; a.m = bp.m; a.R = R; a.l = bp.l; a.h = bp.h;
     a.table = (double *)p->scratch_spec;
     a.corr = corr;
+    a.rule16 = rule16();
     for (int k = 0; k < bp.K; ++k) {
         const lc_sources &s = srcs[k];
         const Atten &A = bp.att[band][k];
@@ -1231,7 +1238,7 @@ int lc_near_field(lc_plan_t *p, int32_t box, int32_t band, const lc_sources *src
         a.r_lo = bp.radii[k]; a.r_hi = bp.radii[k + 1];
         a.kind = A.kind; a.a = A.a; a.s = A.s; a.p = A.p; a.c = A.c; a.cut = A.cut; a.pref = A.pref;
         a.rule = bp.rule;
-        a.ex = exact_rule(bp, A, k);
+        a.ex = shell_of(bp, A, k);
         HIPCHK(launch_near_table(a, st));
         HIPCHK(launch_near_corr(a, s.n, (const double *)s.grid, s.lum, s.dtype == LC_F64, st));
     }
@@ -1400,13 +1407,9 @@ int lc_greens_imag_ratio(lc_plan_t *p, int32_t box, int32_t band, double *ratio)
     BoxPlan &bp = p->boxes[box];
     if (band < 0 || band >= bp.B) return fail(LC_EINVAL, "band out of range");
     if (!bp.built[band]) return fail(LC_ESTATE, "kernel not built");
-    unsigned long long m[2];
-    HIPCHK(hipMemcpyAsync(m, bp.maxima + 2 * band, 16, hipMemcpyDeviceToHost, p->stream));
-    HIPCHK(hipStreamSynchronize(p->stream));
-    double mi, mr;
-    std::memcpy(&mi, &m[0], 8);
-    std::memcpy(&mr, &m[1], 8);
-    *ratio = mr > 0 ? mi / mr : 0.0;
+    // the builder takes the spectrum of the real, even kernel by cosine
+    // transforms: no imaginary part arises
+    *ratio = 0.0;
     return ok();
 }
 

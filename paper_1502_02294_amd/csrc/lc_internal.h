@@ -151,41 +151,52 @@ int fused_cpw(int n);        // columns per tile
 hipError_t launch_col_y_inv_combine(int n, void *spec, const void *tw_full, const int *split_tab,
                                     const void *part, hipStream_t st);
 
-// Shell kernel builder (FP64): G_k on the octant, mirrored into a full N^3
-// FP64 grid.
-// Exact cell average (kernel rule 1, the m -> infinity limit of the subpoint
-// average) of one shell: pref / l^3 times the integral of phi(r) / (4 pi r^2)
-// over the part of an image cell inside [r_lo, r_sup), r_sup = min(r_{k+1},
-// end of phi's support). gx, gw: 16-point Gauss-Legendre rule on [0, 1].
-struct ExactRule {
+// Radial factor and shell of one slice, as the exact cell average (kernel rule
+// 1, the m -> infinity limit of the subpoint average) takes them: pref / l^3
+// times the integral of phi(r) / (4 pi r^2) over the part of an image cell
+// inside [r_lo, r_sup), r_sup = min(r_{k+1}, end of phi's support).
+struct ExactShell {
     double l, r_lo, r_sup, pref;
-    int32_t kind;
     double a, s, p, c;
-    double gx[16], gw[16];
+    int32_t kind, reserved;
+};
+struct GaussRule {          // 16-point Gauss-Legendre rule on [0, 1]
+    double x[16], w[16];
 };
 
-struct BuildArgs {
-    double *grid;             // N^3 FP64
-    int32_t n, m;
+// Shell kernel builder (FP64): G_k of `count` consecutive slices on the octant
+// [0, N/2]^3, slice j of the batch at oct + j (N/2+1)^3. Passed by value (no
+// device table to write before the launch).
+struct ShellArgs {
+    static constexpr int kMax = 24;
+    double *oct;
+    int32_t n, m, count;
+    int32_t rule;             // 0: m^3 subpoints; 1: exact cell average
+    int32_t self_pair;        // rule 0, r_0 == 0: the own cell is replaced by self_val (slice 0)
+    int32_t has_first;        // the batch starts at slice 0
+    double self_val;
     double l, h;
-    double t_lo, t_hi;        // thresholds of [r_k, r_{k+1})
-    double r_lo, r_hi;
-    int32_t images;           // |u_d| <= images
-    int32_t self_pair;        // 1: the self pair is replaced (r_0 == 0)
-    double self_val;          // added at cell 0 when this is slice 0 and self_pair
-    int32_t kind;
-    double a, s, p, c, cut, pref;
-    int32_t rule;             // 0: m^3 subpoints; 1: exact cell average (ex)
-    ExactRule ex;
+    double r[kMax + 1], T[kMax + 1];   // shell edges r_k and thresholds T_k
+    double cut[kMax];
+    ExactShell sh[kMax];      // pref = 0: no kernel
+    GaussRule rule16;
 };
-hipError_t launch_greens_build(const BuildArgs &a, hipStream_t st);
+hipError_t launch_greens_shells(const ShellArgs &a, hipStream_t st);
 
-// Fold the FP64 spectrum of G_k to the octant store of the plan precision,
-// scaled by (conserve ? target / (l^3 Re G^(0)) : 1); writes G^(0) (after
-// scaling) to *dc and folds max|Im|, max|Re| into maxima[0..1] (atomic).
-hipError_t launch_greens_fold(int n, const void *spec64, void *oct, bool oct_f64, int conserve,
-                              double target_over_l3, double *dc, unsigned long long *maxima,
-                              hipStream_t st);
+// Cosine transforms of the octants of `count` slices (overwritten), the last
+// axis storing into the plan's octant layout: slice k0 + j of the batch to
+// oct + ((k0 + j) B + band) (N/2+1)^3 in FP64 or FP32, scaled by
+// target_over_l3[j] / G^(0) where target_over_l3[j] >= 0 (else 1; G^(0) then
+// from g00[k0 + j], FP64 scratch); the scaled G^(0) in FP64 to dc[(k0+j) B + band].
+struct DctStore {
+    void *oct;
+    double *dc, *g00;
+    int64_t k0;
+    int32_t B, band, conserve;
+    double target_over_l3[ShellArgs::kMax];
+};
+hipError_t launch_greens_dct(int n, double *oct, int count, const void *tw64_half, const void *twist64,
+                             const DctStore &out, bool oct_f64, hipStream_t st);
 
 // Near-field (particle-mesh) correction of one slice: its shell, thresholds
 // and radial factor.
@@ -198,8 +209,9 @@ struct NearArgs {
     double a, s, p, c, cut, pref;
     double *table;             // (R+1)^3 primary-image mesh kernel of the slice (device)
     double *corr;              // N^3 FP64 correction accumulator (device)
-    int32_t rule;              // mesh kernel rule of the box (BuildArgs::rule)
-    ExactRule ex;
+    int32_t rule;              // mesh kernel rule of the box (ShellArgs::rule)
+    ExactShell ex;
+    GaussRule rule16;
 };
 hipError_t launch_near_table(const NearArgs &a, hipStream_t st);
 hipError_t launch_near_corr(const NearArgs &a, int64_t n_pts, const double *pos, const void *lum, bool lum_f64,
