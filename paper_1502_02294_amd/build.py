@@ -14,7 +14,11 @@ ROOT = os.path.dirname(HERE)
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblc.so")
 
-SOURCES = ["lc_xy.hip", "lc_field.hip", "lc_fft.hip", "lc_dct.hip", "lc_greens.hip", "lc_host.cpp"]
+# (source, object, defines): the fused z pass is compiled per group of grid
+# sides, the longest units first
+UNITS = [("lc_fused.hip", f"lc_fused{i}.o", [f"-DLC_FUSED_SET={i}"]) for i in (3, 2, 5, 4, 0, 1)] + \
+        [("lc_xy.hip", "lc_xy.o", []), ("lc_fft.hip", "lc_fft.o", []), ("lc_dct.hip", "lc_dct.o", []),
+         ("lc_field.hip", "lc_field.o", []), ("lc_greens.hip", "lc_greens.o", []), ("lc_host.cpp", "lc_host.o", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-fno-fast-math",
@@ -23,10 +27,11 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-fno-fast-math
           "-Wno-unused-command-line-argument"]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+def _compile(unit, verbose: bool) -> str:
+    src, obj, defines = unit
+    obj = os.path.join(BUILD, obj)
     lang = ["-x", "hip"] if src.endswith(".cpp") else []
-    cmd = [HIPCC] + COMMON + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + COMMON + defines + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -37,10 +42,10 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 6) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        objs = list(ex.map(lambda u: _compile(u, verbose), UNITS))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs
     if verbose:

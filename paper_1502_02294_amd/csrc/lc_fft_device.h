@@ -564,22 +564,21 @@ template <typename T, int L> struct ColShape {
     static constexpr int PAD = 1;
 };
 
-// Launch shape of the fused slice-sum pass: schedule S, 16 columns per
-// workgroup (128-byte rows).
-template <int L, typename S> struct FusedShape {
+// Launch shape of the fused slice-sum pass: schedule S, 16 FP32 or 8 FP64
+// columns per workgroup (128-byte rows).
+template <typename T, int L, typename S> struct FusedShape {
     static constexpr int TPL = S::TPL;
-    // 16 columns (a 128-byte row segment), at most 512 threads (so that a
-    // thread keeps a 256-register budget; a power of two below that), at
-    // least one wave. (8-column tiles at L = 256, two workgroups per CU,
-    // measured slower: half-line reads cost more than the overlap gains.)
-    static constexpr int CMAX = 512 / TPL < 16 ? 512 / TPL : 16;
-    static constexpr int CPW = (16 * TPL >= 64)
+    // a 128-byte row segment, at most 512 threads (so that a thread keeps a
+    // 256-register budget; a power of two below that), at least one wave.
+    // (FP32: 8-column tiles at L = 256, two workgroups per CU, measured
+    // slower: half-line reads cost more than the overlap gains.)
+    static constexpr int CW = sizeof(T) == 4 ? 16 : 8;
+    static constexpr int CMAX = 512 / TPL < CW ? 512 / TPL : CW;
+    static constexpr int CPW = (CW * TPL >= 64)
                                    ? (CMAX >= 16 ? 16 : CMAX >= 8 ? 8 : CMAX >= 4 ? 4 : CMAX >= 2 ? 2 : 1)
                                    : 64 / TPL;
     static constexpr int NT = CPW * TPL;
     static constexpr int PAD = 1;
-    // requested waves per SIMD: bounds the register budget (512 / WPE)
-    static constexpr int WPE = (L / TPL <= 8) ? 4 : 2;
 };
 
 // Launch shape of the row (x) passes for half-length L = N/2.

@@ -258,6 +258,11 @@ struct BoxPlan {
     int dcw = 0;                 // FP64 DC partials per slice (x-pass workgroups, planes or half planes)
     // spectra in the parity y layout (half-plane xy shapes), completed by the fused z pass
     bool parity() const { return use_xy && xy_parity(n, xy_variant); }
+    // plain forms: the fused passes where they exist, one shape per N (not
+    // part of the schedule), in the parity layout at N = 192 and 256
+    bool plain = false;
+    bool plain_xy() const { return plain && xy_supported(n); }
+    bool plain_parity() const { return plain_xy() && yx_inv_supported(n); }
     int dc_width() const { return use_xy ? (parity() ? 2 : 1) * n : xwgs; }
     int64_t dc_cap() const { return std::max<int64_t>(2 * (int64_t)n, xwgs); }   // dcpart entries per slice
 };
@@ -484,7 +489,7 @@ FusedArgs fused_args(const BoxPlan &bp) {
     fa.spec = bp.spec; fa.spec_stride = spec_elems(n); fa.ghat = bp.ghat; fa.oct_stride = oct_elems(n);
     fa.K = bp.K; fa.B = bp.B; fa.band0 = 0; fa.nband = bp.fused_bands;
     for (int j = 0; j < 4; ++j) fa.kcount[j] = j < fa.nband ? bp.kcount[j] : 0;
-    fa.acc = bp.acc; fa.acc_stride = spec_elems(n); fa.zero_dc = 1; fa.kahan = fa.nband <= 2;
+    fa.acc = bp.acc; fa.acc_stride = spec_elems(n); fa.zero_dc = 1;
     fa.part = bp.part; fa.part_stride = bp.part_stride; fa.max_parts = bp.max_parts;
     fa.split_tab = bp.split_tab;
     fa.variant = bp.fused_variant;
@@ -711,6 +716,7 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
         bp.tw64_half = p->ws + o.tw64_half; bp.twist64 = p->ws + o.twist64;
         bp.xwgs = x_pass_wgs(bp.n);
         bp.use_xy = p->prec == LC_PREC_FP32 && xy_supported(bp.n);
+        bp.plain = p->prec != LC_PREC_FP32;
         bp.dcw = bp.dc_width();
 
         // tables
@@ -924,6 +930,40 @@ int lc_build_greens_slices(lc_plan_t *p, int32_t box, int32_t band, const lc_att
     return rc ? rc : ok();
 }
 
+// Slice sum of bands [b, b + nb) in a plain form.
+static FusedArgs plain_args(const lc_plan_t *p, const BoxPlan &bp, int b, int nb, int frozen) {
+    FusedArgs fa{};
+    const size_t cs = p->t_f64 ? 16 : 8;
+    fa.spec = bp.spec; fa.spec_stride = spec_elems(bp.n);
+    fa.ghat = bp.ghat; fa.oct_stride = oct_elems(bp.n);
+    fa.K = bp.K; fa.B = bp.B; fa.band0 = b; fa.nband = nb;
+    for (int j = 0; j < nb; ++j) fa.kcount[j] = bp.kcount[b + j];
+    fa.acc = bp.acc + (size_t)b * spec_elems(bp.n) * cs; fa.acc_stride = spec_elems(bp.n);
+    fa.ring = bp.head; fa.frozen = frozen;
+    fa.parity = bp.plain_parity() ? 1 : 0;
+    return fa;
+}
+
+// Forward x and y passes of `cnt` slices of a plain form into consecutive
+// slots from `spec`.
+static hipError_t plain_forward(const lc_plan_t *p, const BoxPlan &bp, const SrcTab &tab, int cnt, bool in_f64,
+                                char *spec, hipStream_t st) {
+    const int n = bp.n;
+    const int64_t se = spec_elems(n);
+    if (bp.plain_xy()) {
+        // (the input sums of the fused passes go to dcpart, which the plain
+        // forms do not read: their check reads the spectra)
+        if (p->t_f64)
+            return launch_xy64_batch(n, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, bp.tw_full, bp.dcpart,
+                                     bp.dc_cap(), st);
+        return launch_xy_fwd_batch(n, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, bp.tw_full, bp.dcpart,
+                                   bp.dc_cap(), bp.plain_parity() ? xy_first_parity(n) : 0, st);
+    }
+    hipError_t e = launch_x_fwd_batch(n, p->t_f64, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, nullptr, st);
+    if (e != hipSuccess) return e;
+    return launch_col_batch(n, p->t_f64, 1, true, spec, se, cnt, bp.tw_full, st);
+}
+
 // Stage lookback slice `slice` of a box (its ring slot) on the plan's stream.
 static int push_impl(lc_plan_t *p, int box, int slice, const lc_sources *s) {
     BoxPlan &bp = p->boxes[box];
@@ -994,16 +1034,17 @@ static int push_impl(lc_plan_t *p, int box, int slice, const lc_sources *s) {
     // tile order
     const bool s3 = p->prec == LC_PREC_FP32 && bp.spec3d;
     char *fwd = s3 ? p->scratch_spec : spec;
-    if (bp.use_xy) {
-        SrcTab tab;
-        tab.p[0] = in;
+    SrcTab tab;
+    tab.p[0] = in;
+    if (bp.plain) {
+        HIPCHK(plain_forward(p, bp, tab, 1, in_f64, fwd, st));
+    } else if (bp.use_xy) {
         HIPCHK(launch_xy_fwd_batch(n, tab, 1, in_f64, fwd, 0, bp.tw_half, bp.twist, bp.tw_full, dcp, bp.dcw,
                                    bp.xy_variant, st));
     } else {
         HIPCHK(launch_x_fwd(n, p->t_f64, in, in_f64, fwd, bp.tw_half, bp.twist, dcp, st));
         HIPCHK(launch_col(n, p->t_f64, 1, true, fwd, bp.tw_full, st));
     }
-    if (p->prec != LC_PREC_FP32) HIPCHK(launch_col(n, p->t_f64, 2, true, spec, bp.tw_full, st));
     if (s3) HIPCHK(launch_col_z_tiled(n, fwd, spec, bp.tw_full, st));
     bp.pushed[slot] = 1;
     return LC_OK;
@@ -1054,7 +1095,7 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
     if (p->prec == LC_PREC_FP32)
         HIPCHK(launch_dc_reduce(bp.dcpart, K, bp.dcw, bp.sk, bp.status, bp.head, st));
     else
-        HIPCHK(launch_spec_dc(bp.spec, p->t_f64, se, K, bp.sk, bp.status, bp.head, st));
+        HIPCHK(launch_spec_dc(n, bp.spec, p->t_f64, bp.plain_parity(), se, K, bp.sk, bp.status, bp.head, st));
     if (p->prec == LC_PREC_FP32) {
         for (int b = b0; b < b1;) {
             const int nb = std::min(bp.fused_bands, b1 - b);
@@ -1067,7 +1108,7 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
             fa.acc = bp.acc + (size_t)b * se * cs; fa.acc_stride = se;
             fa.part = bp.part; fa.part_stride = bp.part_stride; fa.max_parts = bp.max_parts;
             fa.split_tab = tab;
-            fa.zero_dc = 1; fa.kahan = nb <= 2; fa.variant = bp.fused_variant; fa.rounds = bp.fused_rounds;
+            fa.zero_dc = 1; fa.variant = bp.fused_variant; fa.rounds = bp.fused_rounds;
             fa.parity = bp.parity() ? 1 : 0;
             fa.pre = bp.spec3d ? 1 : 0;
             fa.ring = bp.head;
@@ -1090,18 +1131,23 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
             b += nb;
         }
     } else {
-        for (int b = b0; b < b1; ++b) {
-            char *acc = bp.acc + (size_t)b * se * cs;
-            const size_t rs = p->t_f64 ? 8 : 4;
-            const int kc = bp.kcount[b];
-            if (kc == 0) HIPCHK(launch_fill_bytes(acc, se * cs, st));
-            for (int k = 0; k < kc; ++k)
-                HIPCHK(launch_mac_plain(n, p->t_f64, acc, bp.spec + (size_t)(frozen >= 0 ? frozen : bp.slot(k)) * se * cs,
-                                        bp.ghat + ((size_t)k * bp.B + b) * oct_elems(n) * rs, k == 0, st));
-            HIPCHK(launch_col(n, p->t_f64, 2, false, acc, bp.tw_full, st));
-            HIPCHK(launch_col(n, p->t_f64, 1, false, acc, bp.tw_full, st));
-            HIPCHK(launch_x_inv(n, p->t_f64, acc, outp[b - b0], out_f64, bp.tw_half, bp.twist, inv_n3, nullptr,
-                                st));
+        for (int b = b0; b < b1;) {
+            const int nb = std::min(kPlainBands, b1 - b);
+            HIPCHK(launch_fused_plain(n, p->t_f64, plain_args(p, bp, b, nb, frozen), bp.tw_full, st));
+            for (int j = b; j < b + nb; ++j) {
+                char *acc = bp.acc + (size_t)j * se * cs;
+                if (bp.plain_parity()) {
+                    HIPCHK(p->t_f64 ? launch_yx64_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
+                                                      inv_n3, st)
+                                    : launch_yx_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
+                                                    inv_n3, nullptr, nullptr, nullptr, st));
+                    continue;
+                }
+                HIPCHK(launch_col(n, p->t_f64, 1, false, acc, bp.tw_full, st));
+                HIPCHK(launch_x_inv(n, p->t_f64, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, inv_n3, nullptr,
+                                    st));
+            }
+            b += nb;
         }
     }
     return LC_OK;
@@ -1288,7 +1334,9 @@ static int step_box(lc_plan_t *p, int x, const lc_sources *srcs, void *const *ou
         }
         char *spec = bp.spec + (size_t)slot0 * se * cs;
         double *dcp = p->prec == LC_PREC_FP32 ? bp.dcpart + (size_t)slot0 * bp.dcw : nullptr;
-        if (bp.use_xy) {
+        if (bp.plain) {
+            HIPCHK(plain_forward(p, bp, tab, cnt, s0.dtype == LC_F64, spec, st));
+        } else if (bp.use_xy) {
             HIPCHK(launch_xy_fwd_batch(n, tab, cnt, s0.dtype == LC_F64, spec, se, bp.tw_half, bp.twist, bp.tw_full,
                                        dcp, bp.dcw, bp.xy_variant, st));
         } else {
@@ -1296,7 +1344,6 @@ static int step_box(lc_plan_t *p, int x, const lc_sources *srcs, void *const *ou
                                       dcp, st));
             HIPCHK(launch_col_batch(n, p->t_f64, 1, true, spec, se, cnt, bp.tw_full, st));
         }
-        if (p->prec != LC_PREC_FP32) HIPCHK(launch_col_batch(n, p->t_f64, 2, true, spec, se, cnt, bp.tw_full, st));
         for (int j = 0; j < cnt; ++j) bp.pushed[slot0 + j] = 1;
         k += cnt;
     }
@@ -1484,9 +1531,12 @@ int lc_time_kernel(lc_plan_t *p, int32_t box, int32_t kernel, int32_t reps, doub
                 fa.ring = bp.head;
                 return launch_fused_z(n, fa, bp.tw_full, st);
             }
-            case LC_KERNEL_MAC:
-                return launch_mac_plain(n, p->t_f64, acc0, speck,
-                                        bp.ghat + (size_t)k * bp.B * oct_elems(n) * rs, false, st);
+            case LC_KERNEL_MAC: {
+                // the slice-sum pass over one slice (z transform, product, inverse z)
+                FusedArgs fa = plain_args(p, bp, 0, 1, k);
+                fa.kcount[0] = 1;
+                return launch_fused_plain(n, p->t_f64, fa, bp.tw_full, st);
+            }
             case LC_KERNEL_COL_Z_INV: return launch_col(n, p->t_f64, 2, false, acc0, bp.tw_full, st);
             case LC_KERNEL_COL_Y_INV:
                 return fused ? inv_y_fused(n, acc0, bp.tw_full, bp.split_tab, bp.part, bp.fused_rounds != 0, st)

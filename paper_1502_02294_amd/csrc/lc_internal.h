@@ -62,10 +62,11 @@ hipError_t launch_x_rows_batch(int n, const SrcTab &in, int count, bool in_f64, 
 bool xy_supported(int n);
 int xy_variants(int n);
 bool xy_parity(int n, int variant);
+int xy_first_parity(int n);   // first parity-layout shape, -1 if none
 // Inverse y + x passes and epilogue of one band's FP32 accumulator in the
 // parity layout left by the fused z pass with parity input (rows q and
 // N/2 + q hold U_0 = T[q] + T[q+N/2] and U_1 = W_N^-q (T[q] - T[q+N/2])):
-// out = IDFT(acc) * scale + *mu, N^3 reals (FP32 or FP64). With part
+// out = IDFT(acc) * scale + (mu ? *mu : 0), N^3 reals (FP32 or FP64). With part
 // non-null the second parts of split fused tiles (split_tab) are added.
 bool yx_inv_supported(int n);
 hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
@@ -74,6 +75,14 @@ hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const 
 hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                                const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
                                int64_t dc_stride, int variant, hipStream_t st);
+// The same passes in FP64 (the FP64 form; xy_supported(n)): one shape per N,
+// in the parity layout at N = 192 and 256 (plain_parity), with its inverse.
+// dcpart as for the FP32 pass.
+hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
+                             const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
+                             int64_t dc_stride, hipStream_t st);
+hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
+                           const void *tw_full, double scale, hipStream_t st);
 // Column pass over `count` spectra at spec + i*stride (complex elements).
 hipError_t launch_col_batch(int n, bool t_f64, int axis, bool fwd, void *spec, int64_t stride, int count,
                             const void *tw_full, hipStream_t st);
@@ -101,10 +110,6 @@ hipError_t launch_col(int n, bool t_f64, int axis, bool fwd, void *spec, const v
 // (the last narrower), each tile's N rows contiguous. in != out.
 hipError_t launch_col_z_tiled(int n, const void *in, void *out, const void *tw_full, hipStream_t st);
 
-// Plain multiply-accumulate A (+)= G^ S over one slice (first: A = G^ S).
-hipError_t launch_mac_plain(int n, bool t_f64, void *A, const void *S, const void *ghat, bool first,
-                            hipStream_t st);
-
 // Fused z pass for FP32: for each column of the y-transformed slices,
 // forward z transform of every slice k < kcount[b], multiply by G^_{k,b},
 // sum over k (compensated with one or two bands per launch, plain with
@@ -125,7 +130,6 @@ struct FusedArgs {
     void *split_tab;         // int32 per tile: slot holding its second part, or -1 (written in
                              // stream-K mode only; the rounds mode splits no tile)
     int32_t zero_dc;         // 1: drop the (0,0,0) bin (FP64 mean added later)
-    int32_t kahan;           // 1: compensated sum
     int32_t variant;         // register schedule: 0 default, 1 eight elements per thread
     int32_t rounds;          // 1: whole tiles in rounds instead of the balanced split
     int32_t parity;          // 1: spectra in the parity y layout of the half-plane xy shapes
@@ -143,6 +147,20 @@ bool fused_parity_supported(int n);   // parity-layout input compiled for n
 int fused_default_variant(int n, int nband);   // built-in choice for 1 or 2 bands per launch
 int fused_max_bands(int n);  // bands one fused launch can take: 4 at N = 384, 512, else 2
 hipError_t launch_fused_z(int n, const FusedArgs &a, const void *tw_full, hipStream_t st);
+// The same pass of the plain forms, in FP64 or plain FP32 (spectra, octants
+// and accumulators in that type): plain sums in slice order, one or two bands
+// per launch; of FusedArgs only spec .. kcount, acc, parity, ring and frozen
+// are read.
+constexpr int kPlainBands = 2;
+hipError_t launch_fused_plain(int n, bool t_f64, const FusedArgs &a, const void *tw_full, hipStream_t st);
+// The units the pass is compiled in, by group of grid sides.
+enum class FusedForm { fp32, plain64, plain32 };
+template <int SET>
+hipError_t fused_set_launch(int n, FusedForm form, const FusedArgs &a, const void *tw_full, hipStream_t st);
+#define LC_SET_(I) \
+    template <> hipError_t fused_set_launch<I>(int n, FusedForm form, const FusedArgs &a, const void *tw_full, hipStream_t st);
+LC_SET_(0) LC_SET_(1) LC_SET_(2) LC_SET_(3) LC_SET_(4) LC_SET_(5)
+#undef LC_SET_
 int64_t fused_tiles(int n);  // column tiles of the fused pass (main + nyq)
 int fused_cpw(int n);        // columns per tile
 
@@ -232,10 +250,11 @@ hipError_t launch_dc_reduce(const double *dcpart, int K, int W, double *sk, int 
 hipError_t launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st);
 // out = (j_inst - j) / j elementwise (0 where j == 0), FP64 arithmetic
 hipError_t launch_fdiff(const void *j, const void *j_inst, void *out, int64_t count, bool f64, hipStream_t st);
-// The same sums and check for the plain forms, read from the DC bin of each
-// slot's fully transformed spectrum (spec + s*stride, complex FP64 or FP32):
-// a NaN or infinity anywhere in a slice's sources reaches that bin.
-hipError_t launch_spec_dc(const void *spec, bool f64, int64_t stride, int K, double *sk, int *status, int ring,
+// The same sums and check for the plain forms, read from the (0, 0) bins of
+// the z-planes of each slot's y-transformed spectrum (spec + s*stride, complex
+// FP64 or FP32; the parity layout has two per plane, of its even and odd
+// rows): a NaN or infinity anywhere in a plane's sources reaches its bin.
+hipError_t launch_spec_dc(int n, const void *spec, bool f64, bool parity, int64_t stride, int K, double *sk, int *status, int ring,
                           hipStream_t st);
 
 }  // namespace lc

@@ -1,5 +1,5 @@
 // Forward x and y passes of the 3D transform of Eq. 12 fused per z-plane,
-// for the FP32 form at N in {64, 96, 128, 192, 256}.
+// in FP32 and FP64, at N in {64, 96, 128, 192, 256}.
 //
 // One workgroup owns one z-plane of one slice (N x N reals, at N = 256 a
 // 256 KiB plane whose half spectrum is 264 KiB): it reads the plane once,
@@ -54,6 +54,9 @@ template <int C, int I = 0, typename F> __device__ __forceinline__ void static_f
     }
 }
 
+__device__ __forceinline__ float fma_(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return fma(a, b, c); }
+
 // Launch shape: S8 selects the 8-elements-per-thread schedules (smaller
 // register working set, one more LDS exchange per line), NB_ the number of
 // row batches of the x phase (= column batches of the y phase), NC_ the
@@ -62,7 +65,7 @@ template <int C, int I = 0, typename F> __device__ __forceinline__ void static_f
 // the number of rows a workgroup takes (= the y transform length): N for a
 // whole plane, N/2 for the rows of one parity (y = 2m + s), whose y
 // transform leaves the last radix-2 step of the length-N one to the reader.
-template <int N, bool S8, int NB_, int NC_, int NR_ = N> struct XYShape {
+template <typename T, int N, bool S8, int NB_, int NC_, int NR_ = N> struct XYShape {
     static constexpr int L = N / 2;
     static constexpr int NR = NR_;
     static constexpr int HALVES = N / NR;
@@ -83,7 +86,7 @@ template <int N, bool S8, int NB_, int NC_, int NR_ = N> struct XYShape {
     static constexpr int LDS = XS + NC * RG;
     static_assert(NC >= 0 && NC <= NB, "column batches held in LDS");
     static_assert(HALVES == 1 || HALVES == 2, "whole planes or rows of one parity");
-    static_assert((LDS + 2 * L + 2 * NR) * 8 + NT / 8 <= 160 * 1024, "LDS of one workgroup");
+    static_assert((LDS + 2 * L + 2 * NR) * sizeof(cx<T>) + NT / 8 <= 160 * 1024, "LDS of one workgroup");
     static_assert(NT == TY * CPB, "x and y phases must use the same thread count");
     static_assert(NT % 64 == 0 && NT <= 1024, "whole waves, one workgroup");
     static_assert(CPB % TX == 0, "column batches must hold whole lane groups of a row");
@@ -111,6 +114,12 @@ template <int TX> __device__ __forceinline__ float partner_val(float v) {
     }
 }
 
+template <int TX> __device__ __forceinline__ double partner_val(double v) {
+    const int lo = __float_as_int(partner_val<TX>(__int_as_float(__double2loint(v))));
+    const int hi = __float_as_int(partner_val<TX>(__int_as_float(__double2hiint(v))));
+    return __hiloint2double(hi, lo);
+}
+
 // Element index, in the same thread or in lane TX - t, holding the partner
 // position L - q of the element e of the last x pass. Output positions of the
 // last pass are q = t + i*TX + r*M (e = i*RL + r, M = L/RL = BPT*TX).
@@ -128,36 +137,38 @@ __device__ __forceinline__ constexpr int partner_e(int e, bool t0) {
 // sum of every row batch down to their uses in the y phase, which keeps the
 // inputs of all batches live together and spills them.
 __device__ __forceinline__ void pin(cx<float> &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void pin(cx<double> &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 __device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }
 
-template <int N, int NR_, typename TIN, bool S8, int NB_, int NC_, bool PER>
-__global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_kernel(
-    SrcTab srcs, cx<float> *__restrict__ spec0, int64_t spec_stride, const cx<float> *__restrict__ tw_half,
-    const cx<float> *__restrict__ twist, const cx<float> *__restrict__ tw_full, double *__restrict__ dcpart,
+template <typename T, int N, int NR_, typename TIN, bool S8, int NB_, int NC_, bool PER>
+__global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_kernel(
+    SrcTab srcs, cx<T> *__restrict__ spec0, int64_t spec_stride, const cx<T> *__restrict__ tw_half,
+    const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double *__restrict__ dcpart,
     int64_t dc_stride, int n_planes) {
-    using SH = XYShape<N, S8, NB_, NC_, NR_>;
+    using SH = XYShape<T, N, S8, NB_, NC_, NR_>;
     constexpr int L = SH::L, TX = SH::TX, NB = SH::NB, RPB = SH::RPB, CPB = SH::CPB, NT = SH::NT;
     constexpr int NR = SH::NR, HALVES = SH::HALVES;
     constexpr int SK = SH::SK, LSX = SH::LSX, ES = SH::ES, NC = SH::NC, XS = SH::XS, RG = SH::RG;
-    constexpr bool F32IN = std::is_same<TIN, float>::value;
-    static_assert(!PER || F32IN, "the persistent form reads FP32 grids");
+    // input that converts exactly is summed (FP64 mean) as it is read
+    constexpr bool EXIN = sizeof(TIN) <= sizeof(T);
+    static_assert(!PER || sizeof(T) == 4 && EXIN, "the persistent form reads FP32 grids");
     // Row batches in flight ahead of their transform. One workgroup per
-    // plane: two batches (FP32 input) or one (FP64 input, whose loads are
-    // twice as wide). Persistent workgroups: the first half of the next
+    // plane: two batches, or one of FP64 input to the FP32 form (whose loads
+    // are twice as wide). Persistent workgroups: the first half of the next
     // plane is fetched during the last column batches of the current one's
     // y phase, the second half half a plane ahead during its x phase (more
     // would not fit in registers without spills, whose reloads would wait
     // for the loads in flight).
-    constexpr int PF = PER ? (NB + 1) / 2 : (F32IN ? (NB < 2 ? NB : 2) : 1);
-    using EX = Engine<float, L, true, typename SH::SX, SK>;
-    using EY = Engine<float, NR, true, typename SH::SY>;
+    constexpr int PF = PER ? (NB + 1) / 2 : (EXIN ? (NB < 2 ? NB : 2) : 1);
+    using EX = Engine<T, L, true, typename SH::SX, SK>;
+    using EY = Engine<T, NR, true, typename SH::SY>;
     constexpr int EXN = EX::E, EYN = EY::E;
     constexpr int RL = EX::RL, BPTL = EX::PLs::BPT, M = L / RL;
     static_assert(BPTL * TX == M, "last x pass layout");
 
-    __shared__ cx<float> lds[SH::LDS];
-    __shared__ cx<float> twx[L], twt[L], twy[NR];
-    __shared__ cx<float> zb[NR];
+    __shared__ cx<T> lds[SH::LDS];
+    __shared__ cx<T> twx[L], twt[L], twy[NR];
+    __shared__ cx<T> zb[NR];
     __shared__ double red[NT / 64];
 
     const int tid = threadIdx.x;
@@ -171,7 +182,7 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
     // `late`, the address passes through an empty asm statement so that the
     // loads stay after the preceding barrier instead of being hoisted to
     // where their registers are still taken
-    auto load_batch = [&](auto bc, int pl, cx<float>(&dst)[NB][EXN], bool late) {
+    auto load_batch = [&](auto bc, int pl, cx<T>(&dst)[NB][EXN], bool late) {
         constexpr int b = decltype(bc)::value;
         if constexpr (b < NB) {
             // (the offset, not the pointer, goes through the asm: the pointer
@@ -184,19 +195,19 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
 #pragma unroll
             for (int e = 0; e < EXN; ++e) {
                 const cx<TIN> v = *(const cx<TIN> *)(row + 2 * EX::in_pos(xt, e));
-                dst[b][e] = mk((float)v.x, (float)v.y);
+                dst[b][e] = mk((T)v.x, (T)v.y);
             }
         }
     };
 
     int plane = blockIdx.x;
-    cx<float> xr[NB][EXN];
+    cx<T> xr[NB][EXN];
     static_for<PF>([&](auto bc) { load_batch(bc, plane, xr, false); });
     // untangle twist as V_q = -i W^q / 2:  Y[q] = (A + conj B) / 2 + V_q (A - conj B)
     for (int i = tid; i < L; i += NT) {
         twx[i] = tw_half[i];
-        const cx<float> w = twist[i];
-        twt[i] = mk(0.5f * w.y, -0.5f * w.x);
+        const cx<T> w = twist[i];
+        twt[i] = mk((T)0.5 * w.y, (T)-0.5 * w.x);
     }
     for (int i = tid; i < NR; i += NT) twy[i] = tw_full[HALVES * i];   // W_NR^i = W_N^(HALVES i)
 
@@ -204,48 +215,48 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
         // plane unit: slice, z-plane and row parity (rows y = HALVES m + par);
         // its y-transformed rows go to rows par*NR .. par*NR + NR-1
         const int slice = plane / (N * HALVES), z = (plane % (N * HALVES)) / HALVES, par = plane % HALVES;
-        cx<float> *__restrict__ mainp = spec0 + slice * spec_stride + ((int64_t)z * N + par * NR) * L;
-        cx<float> *__restrict__ nyq = spec0 + slice * spec_stride + spec_main(N) + (int64_t)z * N + par * NR;
+        cx<T> *__restrict__ mainp = spec0 + slice * spec_stride + ((int64_t)z * N + par * NR) * L;
+        cx<T> *__restrict__ nyq = spec0 + slice * spec_stride + spec_main(N) + (int64_t)z * N + par * NR;
         const int next = plane + stride;
         const bool has_next = PER && next < n_planes;
-        cx<float> xn[NB][EXN];   // the next plane's rows (persistent form)
+        cx<T> xn[NB][EXN];   // the next plane's rows (persistent form)
         double dsum = 0.0;
 
         // ---- 2. x transforms and untangle, one row batch at a time
         static_for<NB>([&](auto bc) {
             constexpr int b = decltype(bc)::value;
             load_batch(std::integral_constant<int, b + PF>{}, plane, xr, true);
-            if constexpr (F32IN) {
-                // FP32 input converts exactly: sum it here, before the batch is
-                // transformed, so the raw values need not stay live
+            if constexpr (EXIN) {
+                // summed here, before the batch is transformed, so that the
+                // raw values need not stay live
 #pragma unroll
                 for (int e = 0; e < EXN; ++e) dsum += (double)xr[b][e].x + (double)xr[b][e].y;
                 pin(dsum);
             }
             EX::run(xr[b], lds, xl * LSX, 1, xt, twx);
-            cx<float> pv[EXN];
+            cx<T> pv[EXN];
 #pragma unroll
             for (int e = 0; e < EXN; ++e) {
-                const cx<float> sv = xr[b][partner_e<RL, BPTL>(e, false)];
-                const cx<float> o = mk(partner_val<TX>(sv.x), partner_val<TX>(sv.y));
+                const cx<T> sv = xr[b][partner_e<RL, BPTL>(e, false)];
+                const cx<T> o = mk(partner_val<TX>(sv.x), partner_val<TX>(sv.y));
                 // (component-wise selects of values: a select between two
                 // cx lvalues becomes a pointer select, which keeps the whole
                 // row array in scratch memory where the partner index is
                 // not a power of two)
-                const cx<float> own = xr[b][partner_e<RL, BPTL>(e, true)];
+                const cx<T> own = xr[b][partner_e<RL, BPTL>(e, true)];
                 pv[e] = mk(t0 ? own.x : o.x, t0 ? own.y : o.y);
             }
 #pragma unroll
             for (int e = 0; e < EXN; ++e) {
                 const int q = EX::out_pos(xt, e);
-                const cx<float> A = xr[b][e], B = pv[e];
+                const cx<T> A = xr[b][e], B = pv[e];
                 if (e == 0 && t0) {
                     // q = 0: Y[0] = Re A + Im A and Y[L] = Re A - Im A, both real: packed
                     xr[b][e] = mk(A.x + A.y, A.x - A.y);
                 } else {
-                    const cx<float> S = mk(A.x + B.x, A.y - B.y), D = mk(A.x - B.x, A.y + B.y);
-                    const cx<float> V = twt[q];
-                    xr[b][e] = mk(fmaf(0.5f, S.x, V.x * D.x - V.y * D.y), fmaf(0.5f, S.y, V.x * D.y + V.y * D.x));
+                    const cx<T> S = mk(A.x + B.x, A.y - B.y), D = mk(A.x - B.x, A.y + B.y);
+                    const cx<T> V = twt[q];
+                    xr[b][e] = mk(fma_((T)0.5, S.x, V.x * D.x - V.y * D.y), fma_((T)0.5, S.y, V.x * D.y + V.y * D.x));
                 }
                 pin(xr[b][e]);
             }
@@ -265,7 +276,7 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
         static_for<NB>([&](auto cbc) {
             constexpr int cb = decltype(cbc)::value;
             // transposed batch: its own region (filled by the x phase) or the scratch
-            cx<float> *reg = cb < NC ? lds + XS + cb * RG : lds;
+            cx<T> *reg = cb < NC ? lds + XS + cb * RG : lds;
             if constexpr (cb >= NC) {
                 lds_barrier();   // earlier readers of the scratch are done
                 static_for<NB>([&](auto bc) {
@@ -288,7 +299,7 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
                     if (has_next) load_batch(std::integral_constant<int, cb - (NB - PF)>{}, next, xn, true);
                 }
             }
-            cx<float> y[EYN];
+            cx<T> y[EYN];
 #pragma unroll
             for (int e = 0; e < EYN; ++e) y[e] = reg[EY::in_pos(yt, e) * ES + yc];
             EY::run(y, reg, yc, ES, yt, twy);
@@ -303,7 +314,7 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
         });
 
         // ---- 4. separate the packed p = 0 / p = N/2 column; FP64 plane sum
-        if constexpr (!F32IN) {
+        if constexpr (!EXIN) {
             // FP64 input: the sum needs the values before rounding; read them again
             const TIN *in = (const TIN *)srcs.p[slice] + (int64_t)z * N * N;
 #pragma unroll
@@ -319,9 +330,9 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
         if (lane == 0) red[tid >> 6] = dsum;
         lds_barrier();
         for (int k = tid; k < NR; k += NT) {
-            const cx<float> A = zb[k], B = zb[(NR - k) % NR];
-            mainp[(int64_t)k * L] = mk((A.x + B.x) * 0.5f, (A.y - B.y) * 0.5f);
-            nyq[k] = mk((A.y + B.y) * 0.5f, (B.x - A.x) * 0.5f);
+            const cx<T> A = zb[k], B = zb[(NR - k) % NR];
+            mainp[(int64_t)k * L] = mk((A.x + B.x) * (T)0.5, (A.y - B.y) * (T)0.5);
+            nyq[k] = mk((A.y + B.y) * (T)0.5, (B.x - A.x) * (T)0.5);
         }
         if (tid == 0) {
             double sum = 0.0;
@@ -358,17 +369,17 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_ke
 //      inverse transform), scaled by 1/N^3, plus the FP64 mean, and stored.
 // With COMBINE the second parts of tiles that the fused pass split between
 // two workgroups (tab, part) are added while loading.
-template <int N, typename TOUT, bool S8, int NB_, bool COMBINE>
-__global__ __launch_bounds__((XYShape<N, S8, NB_, 0, N / 2>::NT)) void yx_inv_kernel(
-    const cx<float> *__restrict__ acc, TOUT *__restrict__ out, const cx<float> *__restrict__ tw_half,
-    const cx<float> *__restrict__ twist, const cx<float> *__restrict__ tw_full, double scale,
-    const double *__restrict__ mu, const int *__restrict__ tab, const cx<float> *__restrict__ part, int cpw_z,
+template <typename T, int N, typename TOUT, bool S8, int NB_, bool COMBINE>
+__global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv_kernel(
+    const cx<T> *__restrict__ acc, TOUT *__restrict__ out, const cx<T> *__restrict__ tw_half,
+    const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double scale,
+    const double *__restrict__ mu, const int *__restrict__ tab, const cx<T> *__restrict__ part, int cpw_z,
     int64_t tiles_main) {
-    using SH = XYShape<N, S8, NB_, 0, N / 2>;
+    using SH = XYShape<T, N, S8, NB_, 0, N / 2>;
     constexpr int L = SH::L, NR = SH::NR, TX = SH::TX, TY = SH::TY, NB = SH::NB, RPB = SH::RPB, CPB = SH::CPB;
     constexpr int NT = SH::NT, SK = SH::SK, LSX = SH::LSX;
-    using EY = Engine<float, NR, false, typename SH::SY>;
-    using EX = Engine<float, L, false, typename SH::SX, SK>;
+    using EY = Engine<T, NR, false, typename SH::SY>;
+    using EX = Engine<T, L, false, typename SH::SX, SK>;
     constexpr int EYN = EY::E, EXN = EX::E;
     constexpr int RLY = EY::RL, BPTY = EY::PLs::BPT;
     static_assert(RPB % TY == 0, "a y output row's batch is fixed by its element index");
@@ -376,22 +387,23 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, 0, N / 2>::NT)) void yx_inv_ke
     constexpr int LSR = L + 1;                   // transposed row batch: [row][p], p = 0 packed
     constexpr int YREG = NR * ESY, RREG = RPB * LSR, XREG = RPB * LSX;
     constexpr int LDSN = YREG > RREG + XREG ? YREG : RREG + XREG;
-    static_assert((LDSN + 2 * L + NR) * 8 <= 80 * 1024, "two workgroups per CU");
-    __shared__ cx<float> lds[LDSN];
-    __shared__ cx<float> twx[L], twt[L], twy[NR];
+    static_assert((LDSN + 2 * L + NR) * sizeof(cx<T>) <= (sizeof(T) == 4 ? 80 : 160) * 1024,
+                  "two workgroups per CU (FP64: one)");
+    __shared__ cx<T> lds[LDSN];
+    __shared__ cx<T> twx[L], twt[L], twy[NR];
 
     const int tid = threadIdx.x;
     const int yc = tid % CPB, yt = tid / CPB;
     const int xl = tid / TX, xt = tid % TX;
     const int z = blockIdx.x / 2, sp = blockIdx.x % 2;
-    const cx<float> *__restrict__ mainp = acc + ((int64_t)z * N + sp * NR) * L;
-    const cx<float> *__restrict__ nyq = acc + spec_main(N) + (int64_t)z * N + sp * NR;
+    const cx<T> *__restrict__ mainp = acc + ((int64_t)z * N + sp * NR) * L;
+    const cx<T> *__restrict__ nyq = acc + spec_main(N) + (int64_t)z * N + sp * NR;
 
     // every column batch of the half plane, loaded up front
-    cx<float> yr[NB][EYN];
-    auto part_at = [&](int64_t zt, int zc) -> cx<float> {
+    cx<T> yr[NB][EYN];
+    auto part_at = [&](int64_t zt, int zc) -> cx<T> {
         const int w = tab[zt];
-        return w >= 0 ? part[((int64_t)w * N + z) * cpw_z + zc] : mk(0.f, 0.f);
+        return w >= 0 ? part[((int64_t)w * N + z) * cpw_z + zc] : mk((T)0, (T)0);
     };
     static_for<NB>([&](auto cbc) {
         constexpr int cb = decltype(cbc)::value;
@@ -400,14 +412,14 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, 0, N / 2>::NT)) void yx_inv_ke
         for (int e = 0; e < EYN; ++e) {
             const int r = EY::in_pos(yt, e);
             if (p != 0) {
-                cx<float> v = mainp[(int64_t)r * L + p];
+                cx<T> v = mainp[(int64_t)r * L + p];
                 if constexpr (COMBINE) {
                     const int64_t cc = (int64_t)(sp * NR + r) * L + p;
                     v = v + part_at(cc / cpw_z, (int)(cc % cpw_z));
                 }
                 yr[cb][e] = v;
             } else {
-                cx<float> a = mainp[(int64_t)r * L], b = nyq[r];
+                cx<T> a = mainp[(int64_t)r * L], b = nyq[r];
                 if constexpr (COMBINE) {
                     const int64_t cc = (int64_t)(sp * NR + r) * L;
                     a = a + part_at(cc / cpw_z, (int)(cc % cpw_z));
@@ -432,8 +444,8 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, 0, N / 2>::NT)) void yx_inv_ke
     });
 
     // ---- 2. per row batch: transpose, C2R x transform, epilogue
-    const double m = *mu;
-    cx<float> *rreg = lds, *xreg = lds + RREG;
+    const double m = mu ? *mu : 0.0;
+    cx<T> *rreg = lds, *xreg = lds + RREG;
     static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
         lds_barrier();   // earlier readers of the row and exchange regions are done
@@ -447,21 +459,21 @@ __global__ __launch_bounds__((XYShape<N, S8, NB_, 0, N / 2>::NT)) void yx_inv_ke
             }
         });
         lds_barrier();
-        const cx<float> *row = rreg + xl * LSR;
-        cx<float> zx[EXN];
+        const cx<T> *row = rreg + xl * LSR;
+        cx<T> zx[EXN];
 #pragma unroll
         for (int e = 0; e < EXN; ++e) {
             const int q = EX::in_pos(xt, e);
             if (q == 0) {
-                const cx<float> pk = row[0];   // (Y[y][0], Y[y][N/2]), both real
+                const cx<T> pk = row[0];   // (Y[y][0], Y[y][N/2]), both real
                 zx[e] = mk(pk.x + pk.y, pk.x - pk.y);
             } else {
                 // Z[q] = E'_q + i O'_q,  E'_q = X[q] + conj X[L-q],  O'_q = (X[q] - conj X[L-q]) conj(W^q)
-                const cx<float> Xp = row[q], Xm = row[L - q];
-                const cx<float> Ep = mk(Xp.x + Xm.x, Xp.y - Xm.y);
-                const cx<float> Dp = mk(Xp.x - Xm.x, Xp.y + Xm.y);
-                const cx<float> w = twt[q];
-                const cx<float> Op = mk(Dp.x * w.x + Dp.y * w.y, Dp.y * w.x - Dp.x * w.y);
+                const cx<T> Xp = row[q], Xm = row[L - q];
+                const cx<T> Ep = mk(Xp.x + Xm.x, Xp.y - Xm.y);
+                const cx<T> Dp = mk(Xp.x - Xm.x, Xp.y + Xm.y);
+                const cx<T> w = twt[q];
+                const cx<T> Op = mk(Dp.x * w.x + Dp.y * w.y, Dp.y * w.x - Dp.x * w.y);
                 zx[e] = mk(Ep.x - Op.y, Ep.y + Op.x);
             }
         }
@@ -486,12 +498,12 @@ static hipError_t yx_inv_t(const void *acc, void *out, bool out_f64, const void 
                            const void *part, hipStream_t st) {
     constexpr bool S8 = false;
     constexpr int NB = 4;
-    using SH = XYShape<N, S8, NB, 0, N / 2>;
+    using SH = XYShape<float, N, S8, NB, 0, N / 2>;
     const int cpw = fused_cpw(N);
     const int64_t tiles_main = (int64_t)N * (N / 2) / cpw;
     const dim3 grid(2 * N);
 #define YI_(TOUT, COMB)                                                                                       \
-    hipLaunchKernelGGL((yx_inv_kernel<N, TOUT, S8, NB, COMB>), grid, dim3(SH::NT), 0, st, (const cx<float> *)acc, \
+    hipLaunchKernelGGL((yx_inv_kernel<float, N, TOUT, S8, NB, COMB>), grid, dim3(SH::NT), 0, st, (const cx<float> *)acc, \
                        (TOUT *)out, (const cx<float> *)tw_half, (const cx<float> *)twist,                       \
                        (const cx<float> *)tw_full, scale, mu, split_tab, (const cx<float> *)part, cpw, tiles_main)
     if (part) {
@@ -506,7 +518,6 @@ static hipError_t yx_inv_t(const void *acc, void *out, bool out_f64, const void 
 hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
                          const void *tw_full, double scale, const double *mu, const int *split_tab,
                          const void *part, hipStream_t st) {
-    if (!mu) return hipErrorInvalidValue;
     if (n == 256) return yx_inv_t<256>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
     if (n == 192) return yx_inv_t<192>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
     return hipErrorInvalidValue;
@@ -663,17 +674,17 @@ bool xy_supported(int n) { return n == 64 || n == 96 || n == 128 || n == 192 || 
 // and leave the spectrum in the parity layout that the fused z pass
 // completes.
 int xy_variants(int n) { return n == 256 ? 7 : n == 192 ? 4 : n == 128 ? 2 : xy_supported(n) ? 1 : 0; }
-static int xy_first_parity(int n) { return n == 256 ? 4 : n == 192 ? 2 : -1; }
+int xy_first_parity(int n) { return n == 256 ? 4 : n == 192 ? 2 : -1; }
 bool xy_parity(int n, int variant) {
     const int f = xy_first_parity(n);
     return f >= 0 && variant >= f && variant < xy_variants(n);
 }
 
-template <int N, int NR, typename TIN, bool S8, int NB, int NC, bool PER>
+template <typename T, int N, int NR, typename TIN, bool S8, int NB, int NC, bool PER>
 static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_stride, const void *tw_half,
                        const void *twist, const void *tw_full, double *dcpart, int64_t dc_stride,
                        hipStream_t st) {
-    using SH = XYShape<N, S8, NB, NC, NR>;
+    using SH = XYShape<T, N, S8, NB, NC, NR>;
     const int n_planes = N * (N / NR) * count;
     int grid = n_planes;
     if constexpr (PER) {
@@ -684,7 +695,7 @@ static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_str
             hipDeviceProp_t prop;
             if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
                 return hipErrorInvalidDevice;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, xy_fwd_kernel<N, NR, TIN, S8, NB, NC, PER>,
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER>,
                                                              SH::NT, 0) != hipSuccess ||
                 per_cu < 1)
                 per_cu = 1;
@@ -692,9 +703,9 @@ static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_str
         }
         grid = std::min(grid, slots);
     }
-    hipLaunchKernelGGL((xy_fwd_kernel<N, NR, TIN, S8, NB, NC, PER>), dim3((unsigned)grid), dim3(SH::NT), 0, st, in,
-                       (cx<float> *)spec, spec_stride, (const cx<float> *)tw_half, (const cx<float> *)twist,
-                       (const cx<float> *)tw_full, dcpart, dc_stride, n_planes);
+    hipLaunchKernelGGL((xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER>), dim3((unsigned)grid), dim3(SH::NT), 0, st, in,
+                       (cx<T> *)spec, spec_stride, (const cx<T> *)tw_half, (const cx<T> *)twist,
+                       (const cx<T> *)tw_full, dcpart, dc_stride, n_planes);
     return hipGetLastError();
 }
 
@@ -707,9 +718,9 @@ hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, 
     // FP64-input instances of the other shapes spill)
     if (in_f64) variant = xy_parity(n, variant) ? xy_first_parity(n) : 0;
 #define XS_(N, NR, S8, NB, NC, PER)                                                                            \
-    return in_f64 ? xy_t<N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,       \
+    return in_f64 ? xy_t<float, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,       \
                                                            tw_full, dcpart, dc_stride, st)                        \
-                  : xy_t<N, NR, float, S8, NB, NC, PER>(in, count, spec, spec_stride, tw_half, twist, tw_full,    \
+                  : xy_t<float, N, NR, float, S8, NB, NC, PER>(in, count, spec, spec_stride, tw_half, twist, tw_full,    \
                                                         dcpart, dc_stride, st);
 #define X_(N, S8, NB, NC, PER) XS_(N, N, S8, NB, NC, PER)
 #define XH_(N, S8, NB, NC) XS_(N, N / 2, S8, NB, NC, false)
@@ -737,6 +748,53 @@ hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, 
 #undef XH_
 #undef X_
 #undef XS_
+}
+
+// FP64 shapes: a z-plane's FP64 half spectrum is twice the FP32 one, so whole
+// planes up to N = 128 and half planes (parity layout) at 192 and 256, one
+// workgroup of six or eight waves per CU there. Bound by HBM and by the one
+// workgroup's alternation of reading and computing, as the FP32 whole-plane
+// shapes: at 256^3 74 us a slice, 3.6 TB/s, against 110 us for the separate
+// x and y passes.
+hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
+                             const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
+                             int64_t dc_stride, hipStream_t st) {
+    if (count < 1 || count > SrcTab::kMax || !dcpart) return hipErrorInvalidValue;
+#define XD_(N, NR, S8, NB, NC)                                                                                  \
+    return in_f64 ? xy_t<double, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist, \
+                                                                   tw_full, dcpart, dc_stride, st)              \
+                  : xy_t<double, N, NR, float, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,  \
+                                                                  tw_full, dcpart, dc_stride, st);
+    switch (n) {
+        case 64: XD_(64, 64, false, 1, 0)
+        case 96: XD_(96, 96, false, 1, 0)
+        case 128: XD_(128, 128, true, 2, 0)
+        case 192: XD_(192, 96, false, 2, 0)
+        case 256: XD_(256, 128, true, 4, 1)
+        default: return hipErrorInvalidValue;
+    }
+#undef XD_
+}
+
+template <int N, bool S8, int NB>
+static hipError_t yx64_t(const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
+                         const void *tw_full, double scale, hipStream_t st) {
+    using SH = XYShape<double, N, S8, NB, 0, N / 2>;
+#define YD_(TOUT)                                                                                                   \
+    hipLaunchKernelGGL((yx_inv_kernel<double, N, TOUT, S8, NB, false>), dim3(2 * N), dim3(SH::NT), 0, st,            \
+                       (const cx<double> *)acc, (TOUT *)out, (const cx<double> *)tw_half, (const cx<double> *)twist, \
+                       (const cx<double> *)tw_full, scale, nullptr, nullptr, (const cx<double> *)nullptr, 1, (int64_t)0)
+    if (out_f64) YD_(double);
+    else YD_(float);
+#undef YD_
+    return hipGetLastError();
+}
+
+hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
+                           const void *tw_full, double scale, hipStream_t st) {
+    if (n == 256) return yx64_t<256, true, 4>(acc, out, out_f64, tw_half, twist, tw_full, scale, st);
+    if (n == 192) return yx64_t<192, false, 2>(acc, out, out_f64, tw_half, twist, tw_full, scale, st);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace lc
