@@ -176,6 +176,15 @@ size_t lc_workspace_bytes(const lc_plan_desc *desc);
  * the current device for lc_step; lc_destroy releases them. */
 int lc_plan(const lc_plan_desc *desc, lc_plan_t **out);
 
+/* Enqueue the work of later calls on hip_stream (of the plan's device; NULL =
+ * default stream) instead of the descriptor's stream, ordered after the plan's
+ * work so far (an event on the stream before). A caller whose data are produced
+ * and used on another stream moves the plan there instead of ordering the two
+ * streams around every call. The stream must exist until the plan is moved off
+ * it or destroyed; move before or after a capture, not into one. lc_step's
+ * graph is still captured on the descriptor's stream. */
+int lc_set_stream(lc_plan_t *plan, void *hip_stream);
+
 /* Build G_{k,b} for all K slices of one (box, band) - algorithm steps 2-3:
  * direct summation over images inside the shells (FP64), FP64 forward
  * transform, real part of its non-redundant octant kept (G is real and

@@ -32,7 +32,7 @@ EXPORTED = ["lc_workspace_bytes", "lc_plan", "lc_build_greens", "lc_push_sources
             "lc_field", "lc_step", "lc_check_sources", "lc_destroy", "lc_last_error",
             "lc_greens_imag_ratio", "lc_greens_dc", "lc_time_kernel", "lc_get_schedule",
             "lc_set_schedule", "lc_step_static", "lc_field_frozen", "lc_fdiff", "lc_cosmo_slices",
-            "lc_lw_factors", "lc_build_greens_slices", "lc_near_field"]
+            "lc_lw_factors", "lc_build_greens_slices", "lc_near_field", "lc_set_stream"]
 
 (LC_KERNEL_X_FWD, LC_KERNEL_COL_Y_FWD, LC_KERNEL_COL_Z_FWD, LC_KERNEL_FUSED_Z, LC_KERNEL_MAC,
  LC_KERNEL_COL_Z_INV, LC_KERNEL_COL_Y_INV, LC_KERNEL_X_INV, LC_KERNEL_XY_FWD, LC_KERNEL_YX_INV) = range(10)
@@ -122,6 +122,7 @@ def load():
     L.lc_build_greens_slices.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(lc_atten)]
     L.lc_near_field.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(lc_sources), C.c_int32, C.c_void_p,
                                 C.c_int32]
+    L.lc_set_stream.argtypes = [C.c_void_p, C.c_void_p]
     L.lc_destroy.argtypes = [C.c_void_p]
     L.lc_destroy.restype = None
     L.lc_last_error.restype = C.c_char_p
@@ -133,7 +134,7 @@ def load():
     for name in ["lc_plan", "lc_build_greens", "lc_push_sources", "lc_advance", "lc_field", "lc_step",
                  "lc_check_sources", "lc_greens_imag_ratio", "lc_greens_dc", "lc_time_kernel",
                  "lc_get_schedule", "lc_set_schedule", "lc_step_static", "lc_field_frozen", "lc_fdiff",
-                 "lc_cosmo_slices", "lc_lw_factors", "lc_build_greens_slices", "lc_near_field"]:
+                 "lc_cosmo_slices", "lc_lw_factors", "lc_build_greens_slices", "lc_near_field", "lc_set_stream"]:
         getattr(L, name).restype = C.c_int
     _lib = L
     return L
@@ -270,6 +271,10 @@ def fdiff(j, j_inst, out=None):
     return out
 
 
+def lc_set_stream(plan, stream: int):
+    _check(load().lc_set_stream(plan, stream))
+
+
 def lc_destroy(plan):
     load().lc_destroy(plan)
 
@@ -317,10 +322,13 @@ def check_tensor(t, what: str, *, dtypes, numel=None, device=None, allow_host: b
 
 class Plan:
     """A plan over one or more boxes, with its workspace in a torch uint8
-    tensor on the current device. The library's work runs on a stream of
-    the plan's own (default priority; the legacy default stream cannot be
-    captured into a graph); every call first makes that stream wait for the
-    caller's current stream and makes the current stream wait for it after.
+    tensor on the current device. Every call's work is ordered after the work
+    on torch's current stream, and the current stream's later work after it.
+    The plan owns a stream (`stream`, default priority; the legacy default
+    stream cannot be captured into a graph). Until a program asks for it, the
+    work runs on the current stream itself; from then on it runs on the plan's
+    stream, which waits for the current stream before each call and which the
+    current stream waits for after it.
 
     boxes: sequence of objects with n, box, radii, bands (list), supersample,
     conserve (e.g. lc_inputs.Box).
@@ -350,28 +358,61 @@ class Plan:
         self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         base = self.workspace.data_ptr()
         aligned = (base + 255) // 256 * 256
-        self.stream = torch.cuda.Stream(device=self.device)
+        self._home = torch.cuda.Stream(device=self.device)
+        self._home_raw = self._active = self._home.cuda_stream
+        self._direct = False
         self._enter()
-        desc, arr2 = make_plan_desc(descs, precision, self.stream.cuda_stream, aligned, nbytes,
+        desc, arr2 = make_plan_desc(descs, precision, self._home_raw, aligned, nbytes,
                                     1 if use_graph else 0, 1 if autotune else 0)
         self._keep.append(arr2)
         self.handle = lc_plan(desc)
         self._leave()
+        self._direct = True
 
-    # Order the plan's stream after torch's current stream on entry, and the
-    # current stream after the plan's work on exit. With the plan's stream
+    @property
+    def stream(self):
+        """The plan's own stream. Asking for it moves the plan's work there for
+        good, after the work enqueued so far."""
+        self._settle()
+        return self._home
+
+    def _settle(self):
+        if self._direct:
+            self._direct = False
+            if self._active != self._home_raw and getattr(self, "handle", None):
+                lc_set_stream(self.handle, self._home_raw)
+            self._active = self._home_raw
+
+    # On the current stream itself (_direct) a call needs no ordering: the
+    # event record and the stream wait each way took 34 us per call, more than
+    # most calls. That holds while nobody has the plan's stream object, and on
+    # streams torch owns (they outlive the plan). A capture on a stream the plan
+    # is not on, or a foreign stream, moves the work to the plan's stream first.
+    # There, order the plan's stream after torch's current stream on entry, and
+    # the current stream after the plan's work on exit. With the plan's stream
     # current (torch.cuda.stream(plan.stream)) both are skipped, so that
     # consecutive calls start without a cross-stream round trip; the caller
     # then orders the plan's stream against its other streams itself.
     def _enter(self):
         cur = self.torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            self.stream.wait_stream(cur)
+        raw = cur.cuda_stream
+        if self._direct:
+            if raw == self._active:
+                return
+            if (raw == 0 or cur.stream_id != raw) and not self.torch.cuda.is_current_stream_capturing():
+                lc_set_stream(self.handle, raw)
+                self._active = raw
+                return
+            self._settle()
+        if raw != self._home_raw:
+            self._home.wait_stream(cur)
 
     def _leave(self):
+        if self._direct:
+            return
         cur = self.torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            cur.wait_stream(self.stream)
+        if cur.cuda_stream != self._home_raw:
+            cur.wait_stream(self._home)
 
     def _call(self, fn, *args):
         """One library call ordered against torch's current stream (also when
@@ -612,7 +653,14 @@ class Plan:
         """Destroy the plan and drop its workspace (after the plan's stream
         has finished with it)."""
         if getattr(self, "handle", None):
-            self.stream.synchronize()
+            cur = self.torch.cuda.current_stream(self.device).cuda_stream
+            if self._direct and cur == self._active and self.torch.cuda.is_current_stream_capturing():
+                # a capture began on the stream the plan's work went to: what was
+                # enqueued there before it cannot be waited for on the plan's stream
+                # without joining it to the capture
+                self._direct = False
+            else:
+                self.stream.synchronize()   # (after the work on any stream before)
             lc_destroy(self.handle)
             self.handle = None
         self.workspace = None

@@ -270,7 +270,9 @@ struct BoxPlan {
 struct lc_plan_s {
     int prec = LC_PREC_FP64;
     bool t_f64 = true;
-    hipStream_t stream = nullptr;
+    hipStream_t stream = nullptr;    // calls enqueue here (lc_set_stream); at first the descriptor's
+    hipStream_t home = nullptr;      // the descriptor's stream: lc_step's graph is captured on it
+    hipEvent_t moved = nullptr;      // lc_set_stream: end of the work on the stream before
     char *ws = nullptr;
     size_t ws_bytes = 0;
     int use_graph = 0;
@@ -290,6 +292,7 @@ struct lc_plan_s {
     std::vector<hipEvent_t> side_done;
     hipEvent_t fork = nullptr;
     ~lc_plan_s() {
+        if (moved) (void)hipEventDestroy(moved);
         for (hipEvent_t e : side_done) (void)hipEventDestroy(e);
         if (fork) (void)hipEventDestroy(fork);
         for (hipStream_t t : side) (void)hipStreamDestroy(t);
@@ -670,7 +673,7 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
     std::unique_ptr<lc_plan_s> p(new lc_plan_s());
     p->prec = d->precision;
     p->t_f64 = d->precision == LC_PREC_FP64;
-    p->stream = (hipStream_t)d->hip_stream;
+    p->stream = p->home = (hipStream_t)d->hip_stream;
     p->ws = (char *)d->workspace;
     p->ws_bytes = d->workspace_bytes;
     p->use_graph = d->use_graph;
@@ -804,6 +807,17 @@ void lc_destroy(lc_plan_t *p) {
 }
 
 const char *lc_last_error(void) { return g_err.c_str(); }
+
+int lc_set_stream(lc_plan_t *p, void *hip_stream) {
+    if (!p) return fail(LC_EINVAL, "plan is NULL");
+    hipStream_t to = (hipStream_t)hip_stream;
+    if (to == p->stream) return ok();
+    if (!p->moved) HIPCHK(hipEventCreateWithFlags(&p->moved, hipEventDisableTiming));
+    HIPCHK(hipEventRecord(p->moved, p->stream));
+    HIPCHK(hipStreamWaitEvent(to, p->moved, 0));
+    p->stream = to;
+    return ok();
+}
 
 }  // extern "C"
 
@@ -1438,10 +1452,13 @@ int lc_step(lc_plan_t *p, const lc_sources *srcs, void *const *out, int32_t dtyp
     if (!p->gexec || key != p->gkey) {
         if (p->gexec) { (void)hipGraphExecDestroy(p->gexec); p->gexec = nullptr; }
         if (p->graph) { (void)hipGraphDestroy(p->graph); p->graph = nullptr; }
-        HIPCHK(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
+        HIPCHK(hipStreamBeginCapture(p->home, hipStreamCaptureModeThreadLocal));
+        hipStream_t on = p->stream;
+        p->stream = p->home;
         int rc = step_impl(p, srcs, out, dtype);
+        p->stream = on;
         hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(p->stream, &g);
+        hipError_t e = hipStreamEndCapture(p->home, &g);
         if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
         if (e != hipSuccess) return fail(LC_EDEVICE, "graph capture failed: %s", hipGetErrorString(e));
         p->graph = g;
