@@ -757,6 +757,8 @@ int lc_plan(const lc_plan_desc *d, lc_plan_t **out) {
         HIPCHK(launch_fill_bytes(bp.spec, (int64_t)bp.K * spec_elems(n) * cs, p->stream));
         HIPCHK(launch_fill_f64(bp.dcpart, (int64_t)bp.K * bp.dc_cap(), 0.0, p->stream));
         HIPCHK(launch_fill_f64(bp.ghat0, (int64_t)bp.K * bp.B, 0.0, p->stream));
+        // (the plain forms' fields carry their mean themselves: these stay zero)
+        HIPCHK(launch_fill_f64(bp.mu, bp.B, 0.0, p->stream));
         HIPCHK(launch_fill_i32(bp.status, 1, 0, p->stream));
         HIPCHK(launch_fill_i32(bp.status + 1, 1, INT32_MAX, p->stream));
         p->boxes.push_back(std::move(bp));
@@ -1156,9 +1158,9 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
                 char *acc = bp.acc + (size_t)j * se * cs;
                 if (bp.plain_parity()) {
                     HIPCHK(p->t_f64 ? launch_yx64_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
-                                                      inv_n3, st)
+                                                      inv_n3, bp.mu + j, st)
                                     : launch_yx_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
-                                                    inv_n3, nullptr, nullptr, nullptr, st));
+                                                    inv_n3, bp.mu + j, nullptr, nullptr, st));
                     continue;
                 }
                 HIPCHK(launch_col(n, p->t_f64, 1, false, acc, bp.tw_full, st));

@@ -66,7 +66,7 @@ int xy_first_parity(int n);   // first parity-layout shape, -1 if none
 // Inverse y + x passes and epilogue of one band's FP32 accumulator in the
 // parity layout left by the fused z pass with parity input (rows q and
 // N/2 + q hold U_0 = T[q] + T[q+N/2] and U_1 = W_N^-q (T[q] - T[q+N/2])):
-// out = IDFT(acc) * scale + (mu ? *mu : 0), N^3 reals (FP32 or FP64). With part
+// out = IDFT(acc) * scale + *mu, N^3 reals (FP32 or FP64). With part
 // non-null the second parts of split fused tiles (split_tab) are added.
 bool yx_inv_supported(int n);
 hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
@@ -82,7 +82,7 @@ hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, vo
                              const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
                              int64_t dc_stride, hipStream_t st);
 hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                           const void *tw_full, double scale, hipStream_t st);
+                           const void *tw_full, double scale, const double *mu, hipStream_t st);
 // Column pass over `count` spectra at spec + i*stride (complex elements).
 hipError_t launch_col_batch(int n, bool t_f64, int axis, bool fwd, void *spec, int64_t stride, int count,
                             const void *tw_full, hipStream_t st);

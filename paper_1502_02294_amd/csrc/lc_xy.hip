@@ -444,7 +444,7 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
     });
 
     // ---- 2. per row batch: transpose, C2R x transform, epilogue
-    const double m = mu ? *mu : 0.0;
+    const double m = *mu;
     cx<T> *rreg = lds, *xreg = lds + RREG;
     static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
@@ -518,6 +518,7 @@ static hipError_t yx_inv_t(const void *acc, void *out, bool out_f64, const void 
 hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
                          const void *tw_full, double scale, const double *mu, const int *split_tab,
                          const void *part, hipStream_t st) {
+    if (!mu) return hipErrorInvalidValue;
     if (n == 256) return yx_inv_t<256>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
     if (n == 192) return yx_inv_t<192>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
     return hipErrorInvalidValue;
@@ -778,12 +779,12 @@ hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, vo
 
 template <int N, bool S8, int NB>
 static hipError_t yx64_t(const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                         const void *tw_full, double scale, hipStream_t st) {
+                         const void *tw_full, double scale, const double *mu, hipStream_t st) {
     using SH = XYShape<double, N, S8, NB, 0, N / 2>;
 #define YD_(TOUT)                                                                                                   \
     hipLaunchKernelGGL((yx_inv_kernel<double, N, TOUT, S8, NB, false>), dim3(2 * N), dim3(SH::NT), 0, st,            \
                        (const cx<double> *)acc, (TOUT *)out, (const cx<double> *)tw_half, (const cx<double> *)twist, \
-                       (const cx<double> *)tw_full, scale, nullptr, nullptr, (const cx<double> *)nullptr, 1, (int64_t)0)
+                       (const cx<double> *)tw_full, scale, mu, nullptr, (const cx<double> *)nullptr, 1, (int64_t)0)
     if (out_f64) YD_(double);
     else YD_(float);
 #undef YD_
@@ -791,9 +792,10 @@ static hipError_t yx64_t(const void *acc, void *out, bool out_f64, const void *t
 }
 
 hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                           const void *tw_full, double scale, hipStream_t st) {
-    if (n == 256) return yx64_t<256, true, 4>(acc, out, out_f64, tw_half, twist, tw_full, scale, st);
-    if (n == 192) return yx64_t<192, false, 2>(acc, out, out_f64, tw_half, twist, tw_full, scale, st);
+                           const void *tw_full, double scale, const double *mu, hipStream_t st) {
+    if (!mu) return hipErrorInvalidValue;
+    if (n == 256) return yx64_t<256, true, 4>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, st);
+    if (n == 192) return yx64_t<192, false, 2>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, st);
     return hipErrorInvalidValue;
 }
 
