@@ -34,7 +34,7 @@ HBM_PEAK_GBPS = 8000.0
 METRIC = "retarded-field cell-updates/s (cells×slices/s) + HBM GB/s vs peak; FP32 vs FP64"
 SRC_FILES = ["lc_fft_device.h", "lc_fft.hip", "lc_xy.hip", "lc_field.hip", "lc_fused_device.h", "lc_fused.hip",
              "lc_dct.hip", "lc_greens.hip", "lc_host.cpp",
-             "lc_internal.h"]
+             "lc_greens.h", "lc_internal.h"]
 
 
 def log(*a):

@@ -17,6 +17,7 @@
 //           plan's octant store (TO, main [r][q][p < N/2] then p = N/2 as
 //           [r][q]), scaled for the conserve option, G^(0) to dc
 #include "lc_fft_device.h"
+#include "lc_greens.h"
 #include "lc_internal.h"
 
 namespace lc {

@@ -12,6 +12,7 @@
 #include <algorithm>
 
 #include "lc_fft_device.h"
+#include "lc_greens.h"
 #include "lc_internal.h"
 
 namespace lc {
@@ -369,63 +370,79 @@ __device__ __forceinline__ int64_t wrap_node(double c, int n) {
     return (int64_t)v;
 }
 
+// Primary-image mesh kernels of a batch of slices, eight lanes per entry (the
+// m^3 subpoints; the exact rule has one lane work).
 __global__ __launch_bounds__(256) void near_table_kernel(NearArgs a) {
-    const int R = a.R, W = R + 1;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)W * W * W) return;
-    const int d0 = (int)(e / (W * W)), d1 = (int)((e / W) % W), d2 = (int)(e % W);
-    const int m = a.m;
+    const int R = a.R, W = R + 1, W3 = W * W * W;
+    const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 8;
+    const int sub = threadIdx.x % 8;
+    if (e >= (int64_t)a.count * W3) return;   // (all eight lanes together)
+    const int k = (int)(e / W3), o = (int)(e % W3);
+    const int d0 = o / (W * W), d1 = (o / W) % W, d2 = o % W;
+    const int m = a.m, m3 = m * m * m;
     const double four_pi = 12.566370614359172954;
-    const double wm = a.pref / ((double)m * m * m);
+    const ExactShell &f = a.sh[k];
     double acc = 0.0;
-    if ((d0 | d1 | d2) && a.rule == 1) {
+    if (a.rule == 1) {
         const double l = a.l;
-        acc = cell_exact(a.ex, a.rule16, (d0 - 0.5) * l, (d0 + 0.5) * l, (d1 - 0.5) * l, (d1 + 0.5) * l, (d2 - 0.5) * l,
-                         (d2 + 0.5) * l);
+        if ((d0 | d1 | d2) && sub == 0)
+            acc = cell_exact(f, a.rule16, (d0 - 0.5) * l, (d0 + 0.5) * l, (d1 - 0.5) * l, (d1 + 0.5) * l, (d2 - 0.5) * l,
+                             (d2 + 0.5) * l);
     } else if (d0 | d1 | d2) {
-        for (int a0 = 0; a0 < m; ++a0) {
+        const double wm = f.pref / (double)m3, t_lo = a.t_lo[k], t_hi = a.t_hi[k];
+        for (int s = sub; s < m3; s += 8) {
+            const int a0 = s / (m * m), a1 = (s / m) % m, a2 = s % m;
             const int64_t q0 = 2 * m * (int64_t)d0 + (2 * a0 + 1 - m);
-            for (int a1 = 0; a1 < m; ++a1) {
-                const int64_t q1 = 2 * m * (int64_t)d1 + (2 * a1 + 1 - m);
-                for (int a2 = 0; a2 < m; ++a2) {
-                    const int64_t q2 = 2 * m * (int64_t)d2 + (2 * a2 + 1 - m);
-                    const double dn = (double)(q0 * q0 + q1 * q1 + q2 * q2);
-                    if (dn >= a.t_lo && dn < a.t_hi) {
-                        const double rho = sqrt(dn) * a.h;
-                        acc += wm * phi_eval(a.kind, rho, a.a, a.s, a.p, a.c, a.cut) / (four_pi * rho * rho);
-                    }
-                }
+            const int64_t q1 = 2 * m * (int64_t)d1 + (2 * a1 + 1 - m);
+            const int64_t q2 = 2 * m * (int64_t)d2 + (2 * a2 + 1 - m);
+            const double dn = (double)(q0 * q0 + q1 * q1 + q2 * q2);
+            if (dn >= t_lo && dn < t_hi) {
+                const double rho = sqrt(dn) * a.h;
+                acc += wm * phi_eval(f.kind, rho, f.a, f.s, f.p, f.c, a.cut[k]) / (four_pi * rho * rho);
             }
         }
+#pragma unroll
+        for (int x = 4; x > 0; x >>= 1) acc += __shfl_xor(acc, x, 64);
     }
-    a.table[e] = acc;
+    if (sub == 0) a.table[e] = acc;
 }
 
-template <typename TL>
-__global__ __launch_bounds__(256) void near_corr_kernel(NearArgs a, int64_t n_pts, const double *__restrict__ pos,
-                                                        const TL *__restrict__ lum) {
+// Corrections of a batch of slices: work item = (slice, source, offset).
+__global__ __launch_bounds__(256) void near_corr_kernel(NearArgs a) {
+    __shared__ int64_t first[NearArgs::kMax + 1];
+    if ((int)threadIdx.x <= a.count) first[threadIdx.x] = a.first[threadIdx.x];
+    __syncthreads();
     const int R = a.R, D = 2 * R + 1, W = R + 1;
     const int64_t V = (int64_t)D * D * D;
     const int n = a.n;
     const double four_pi = 12.566370614359172954;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_pts * V;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t s = e / V;
+    const int64_t total = first[a.count] * V;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t g = e / V;
         const int o = (int)(e % V);
         const int o0 = o / (D * D) - R, o1 = (o / D) % D - R, o2 = o % D - R;
         if (!(o0 | o1 | o2)) continue;
+        int k = 0, hi = a.count - 1;      // slice of source g
+        while (k < hi) {
+            const int mid = (k + hi + 1) / 2;
+            if (first[mid] <= g) k = mid;
+            else hi = mid - 1;
+        }
+        const int64_t s = g - first[k];
+        const double *__restrict__ pos = a.pos[k];
         const double p0 = pos[3 * s], p1 = pos[3 * s + 1], p2 = pos[3 * s + 2];
         // a non-finite position has no cell (its slice is flagged by the deposit)
         if (!isfinite(p0) || !isfinite(p1) || !isfinite(p2)) continue;
-        const double L = (double)lum[s];
+        const double L = a.lum_f64[k] ? ((const double *)a.lum[k])[s] : (double)((const float *)a.lum[k])[s];
         const double c0 = floor(p0 / a.l + 0.5), c1 = floor(p1 / a.l + 0.5), c2 = floor(p2 / a.l + 0.5);
         const double y0 = (c0 + o0) * a.l - p0, y1 = (c1 + o1) * a.l - p1, y2 = (c2 + o2) * a.l - p2;
         const double rho = sqrt(y0 * y0 + y1 * y1 + y2 * y2);
+        const ExactShell &f = a.sh[k];
         double F = 0.0;
-        if (rho >= a.r_lo && rho < a.r_hi)
-            F = a.pref * phi_eval(a.kind, rho, a.a, a.s, a.p, a.c, a.cut) / (four_pi * rho * rho);
+        if (rho >= f.r_lo && rho < a.r_hi[k])
+            F = f.pref * phi_eval(f.kind, rho, f.a, f.s, f.p, f.c, a.cut[k]) / (four_pi * rho * rho);
         const int t0 = o0 < 0 ? -o0 : o0, t1 = o1 < 0 ? -o1 : o1, t2 = o2 < 0 ? -o2 : o2;
-        const double M = a.table[((int64_t)t0 * W + t1) * W + t2];
+        const double M = a.table[(((int64_t)k * W + t0) * W + t1) * W + t2];
         const double dv = L * (F - M);
         if (dv == 0.0) continue;
         const int64_t cell =
@@ -463,24 +480,14 @@ __global__ __launch_bounds__(256) void add_grid_kernel(TO *__restrict__ out, con
         if (corr[e] != 0.0) out[e] = (TO)((double)out[e] + corr[e]);
 }
 
-hipError_t launch_near_table(const NearArgs &a, hipStream_t st) {
-    const int64_t cells = (int64_t)(a.R + 1) * (a.R + 1) * (a.R + 1);
-    hipLaunchKernelGGL(near_table_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_near_corr(const NearArgs &a, int64_t n_pts, const double *pos, const void *lum, bool lum_f64,
-                            hipStream_t st) {
-    if (n_pts <= 0) return hipSuccess;
-    const int64_t D = 2 * a.R + 1;
-    const int64_t work = n_pts * D * D * D;
+hipError_t launch_near(const NearArgs &a, hipStream_t st) {
+    if (a.count < 1 || a.count > NearArgs::kMax) return hipErrorInvalidValue;
+    const int64_t W = a.R + 1, D = 2 * a.R + 1;
+    const int64_t lanes = 8 * a.count * W * W * W;
+    hipLaunchKernelGGL(near_table_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, a);
+    const int64_t work = a.first[a.count] * D * D * D;
     const int wgs = (int)std::min<int64_t>((work + 255) / 256, 16384);
-    if (lum_f64)
-        hipLaunchKernelGGL(near_corr_kernel<double>, dim3(wgs), dim3(256), 0, st, a, n_pts, pos,
-                           (const double *)lum);
-    else
-        hipLaunchKernelGGL(near_corr_kernel<float>, dim3(wgs), dim3(256), 0, st, a, n_pts, pos,
-                           (const float *)lum);
+    hipLaunchKernelGGL(near_corr_kernel, dim3(wgs), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "../../include/lc.h"
+#include "lc_greens.h"
 #include "lc_internal.h"
 
 using namespace lc;
@@ -1291,22 +1292,31 @@ int lc_near_field(lc_plan_t *p, int32_t box, int32_t band, const lc_sources *src
     hipStream_t st = p->stream;
     double *corr = (double *)p->scratch_real;
     HIPCHK(launch_fill_f64(corr, n3, 0.0, st));
-    NearArgs a;
-    a.n = n; a.m = bp.m; a.R = R; a.l = bp.l; a.h = bp.h;
+    NearArgs a{};
+    a.n = n; a.m = bp.m; a.R = R; a.l = bp.l; a.h = bp.h; a.rule = bp.rule;
     a.table = (double *)p->scratch_spec;
     a.corr = corr;
     a.rule16 = rule16();
+    // batches of slices: what a launch's arguments and the table's memory take
+    const int64_t w3 = (int64_t)(R + 1) * (R + 1) * (R + 1);
+    const int cap = (int)std::min<int64_t>(NearArgs::kMax, spec_elems(n) * 16 / (w3 * 8));
     for (int k = 0; k < bp.K; ++k) {
         const lc_sources &s = srcs[k];
         const Atten &A = bp.att[band][k];
-        if (s.n == 0 || k >= bp.kcount[band] || A.pref == 0.0) continue;
-        a.t_lo = bp.T[k]; a.t_hi = bp.T[k + 1];
-        a.r_lo = bp.radii[k]; a.r_hi = bp.radii[k + 1];
-        a.kind = A.kind; a.a = A.a; a.s = A.s; a.p = A.p; a.c = A.c; a.cut = A.cut; a.pref = A.pref;
-        a.rule = bp.rule;
-        a.ex = shell_of(bp, A, k);
-        HIPCHK(launch_near_table(a, st));
-        HIPCHK(launch_near_corr(a, s.n, (const double *)s.grid, s.lum, s.dtype == LC_F64, st));
+        const bool use = s.n > 0 && k < bp.kcount[band] && A.pref != 0.0;
+        if (use) {
+            const int j = a.count++;
+            a.t_lo[j] = bp.T[k]; a.t_hi[j] = bp.T[k + 1];
+            a.r_hi[j] = bp.radii[k + 1]; a.cut[j] = A.cut;
+            a.sh[j] = shell_of(bp, A, k);
+            a.pos[j] = (const double *)s.grid; a.lum[j] = s.lum;
+            a.lum_f64[j] = s.dtype == LC_F64;
+            a.first[j + 1] = a.first[j] + s.n;
+        }
+        if (a.count == cap || (a.count > 0 && k == bp.K - 1)) {
+            HIPCHK(launch_near(a, st));
+            a.count = 0;
+        }
     }
     HIPCHK(launch_add_grid(out, dtype == LC_F64, corr, n3, st));
     return ok();
