@@ -83,4 +83,25 @@ hipError_t launch_deposit(double *grid, int64_t n_pts, const int64_t *cell, cons
 // out = (j_inst - j) / j elementwise (0 where j == 0), FP64 arithmetic
 hipError_t launch_fdiff(const void *j, const void *j_inst, void *out, int64_t count, bool f64, hipStream_t st);
 
+// Device point lists of up to kMax slices of one box, deposited into compact
+// rows instead of dense grids. Row r = z n + y of slice j has its n FP64 cells
+// at rows + slot n, slot = map[j n^2 + r]; slot -1 stands for an empty row. A
+// slice has at most min(points, n^2) rows: the first point that meets an empty
+// row gives it the slot of its own index (slot0[j] + i), or with whole[j]
+// (points >= n^2) row r has slot slot0[j] + r. One launch clears the map and
+// the slots, one deposits (FP64 atomics, as launch_deposit).
+struct PointTab {
+    static constexpr int kMax = 64;
+    const void *where[kMax];   // int64 cells, or with positioned[j] FP64 positions
+    const void *lum[kMax];
+    int64_t first[kMax + 1];   // points before slice j; first[count] = all
+    int32_t slot0[kMax + 1];   // slots before slice j; slot0[count] = all
+    uint8_t lum_f64[kMax], positioned[kMax], whole[kMax];
+    int32_t count, n;
+    double l;
+    int32_t *map;              // count n^2 (16-byte aligned)
+    double *rows;              // slot0[count] n (16-byte aligned)
+};
+hipError_t launch_point_rows(const PointTab &t, hipStream_t st);
+
 }  // namespace lc

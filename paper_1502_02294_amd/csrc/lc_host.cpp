@@ -968,7 +968,7 @@ static FusedArgs plain_args(const lc_plan_t *p, const BoxPlan &bp, int b, int nb
 // Forward x and y passes of `cnt` slices of a plain form into consecutive
 // slots from `spec`.
 static hipError_t plain_forward(const lc_plan_t *p, const BoxPlan &bp, const SrcTab &tab, int cnt, bool in_f64,
-                                char *spec, hipStream_t st) {
+                                char *spec, hipStream_t st, const double *rows = nullptr) {
     const int n = bp.n;
     const int64_t se = spec_elems(n);
     if (bp.plain_xy()) {
@@ -976,13 +976,64 @@ static hipError_t plain_forward(const lc_plan_t *p, const BoxPlan &bp, const Src
         // forms do not read: their check reads the spectra)
         if (p->t_f64)
             return launch_xy64_batch(n, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, bp.tw_full, bp.dcpart,
-                                     bp.dc_cap(), st);
+                                     bp.dc_cap(), st, rows);
         return launch_xy_fwd_batch(n, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, bp.tw_full, bp.dcpart,
-                                   bp.dc_cap(), bp.plain_parity() ? xy_first_parity(n) : 0, st);
+                                   bp.dc_cap(), bp.plain_parity() ? xy_first_parity(n) : 0, st, rows);
     }
     hipError_t e = launch_x_fwd_batch(n, p->t_f64, tab, cnt, in_f64, spec, se, bp.tw_half, bp.twist, nullptr, st);
     if (e != hipSuccess) return e;
     return launch_col_batch(n, p->t_f64, 1, true, spec, se, cnt, bp.tw_full, st);
+}
+
+// Point lists in device memory go through compact rows where the fused x + y
+// pass reads them (3D spectra stage a spectrum in the memory the rows take).
+static bool point_rows(const BoxPlan &bp, const lc_sources &s) {
+    return s.kind != 0 && s.mem == LC_MEM_DEVICE && (bp.use_xy || bp.plain_xy()) && !bp.spec3d;
+}
+
+// Deposit and transform up to `most` of the consecutive slices srcs[0 ..]
+// whose ring slots follow `slot`, all point lists (point_rows): as many as the
+// plan's scratch holds rows for (one always fits: N^2 rows and its map are
+// smaller than the builder's grid and spectrum). Returns the count in *done.
+static int push_point_rows(lc_plan_t *p, BoxPlan &bp, const lc_sources *srcs, int most, int slot, hipStream_t st,
+                           int *done) {
+    const int n = bp.n;
+    const int64_t n2 = (int64_t)n * n;
+    PointTab t{};
+    t.n = n; t.l = bp.l;
+    int64_t bytes = 0;
+    for (int j = 0; j < most && j < PointTab::kMax && point_rows(bp, srcs[j]); ++j) {
+        const lc_sources &s = srcs[j];
+        const int64_t slots = std::min(s.n, n2);
+        bytes += n2 * 4 + slots * n * 8;
+        if (j > 0 && bytes > (int64_t)p->scratch_bytes) break;
+        t.where[j] = s.kind == 1 ? (const void *)s.cell : s.grid;
+        t.lum[j] = s.lum;
+        t.lum_f64[j] = s.dtype == LC_F64;
+        t.positioned[j] = s.kind == 2;
+        t.whole[j] = s.n >= n2;
+        t.first[j + 1] = t.first[j] + s.n;
+        t.slot0[j + 1] = t.slot0[j] + (int32_t)slots;
+        t.count = j + 1;
+    }
+    t.map = (int32_t *)p->scratch_real;
+    t.rows = (double *)(p->scratch_real + t.count * n2 * 4);
+    HIPCHK(launch_point_rows(t, st));
+    SrcTab tab;
+    for (int j = 0; j < t.count; ++j) {
+        tab.p[j] = t.map + j * n2;
+        bp.last_src[slot + j] = nullptr;
+        bp.pushed[slot + j] = 1;
+    }
+    const int64_t se = spec_elems(n);
+    char *spec = bp.spec + (size_t)slot * se * (p->t_f64 ? 16 : 8);
+    if (bp.plain)
+        HIPCHK(plain_forward(p, bp, tab, t.count, true, spec, st, t.rows));
+    else
+        HIPCHK(launch_xy_fwd_batch(n, tab, t.count, true, spec, se, bp.tw_half, bp.twist, bp.tw_full,
+                                   bp.dcpart + (size_t)slot * bp.dcw, bp.dcw, bp.xy_variant, st, t.rows));
+    *done = t.count;
+    return LC_OK;
 }
 
 // Stage lookback slice `slice` of a box (its ring slot) on the plan's stream.
@@ -995,6 +1046,10 @@ static int push_impl(lc_plan_t *p, int box, int slice, const lc_sources *s) {
     bool in_f64 = s->dtype == LC_F64;
     const int slot = bp.slot(slice);
     bp.last_src[slot] = nullptr;
+    if (point_rows(bp, *s)) {
+        int done = 0;
+        return push_point_rows(p, bp, s, 1, slot, st, &done);
+    }
     if (s->kind == 0) {
         if (s->mem == LC_MEM_DEVICE) {
             in = s->grid;
@@ -1333,9 +1388,9 @@ int lc_check_sources(lc_plan_t *p, int32_t box, int32_t *first_bad) {
 }
 
 // One box of lc_step on stream st: its slices' forward passes (groups of up
-// to push_group consecutive dense slices of one value type per batched
-// launch; point lists one by one, through the plan's staging grid, on the
-// plan's stream only) and its field.
+// to push_group consecutive dense slices of one value type, or of point lists,
+// per batched launch; point lists through the plan's scratch, on the plan's
+// stream only) and its field.
 static int step_box(lc_plan_t *p, int x, const lc_sources *srcs, void *const *out, int32_t dtype, hipStream_t st) {
     const size_t cs = p->t_f64 ? 16 : 8;
     BoxPlan &bp = p->boxes[x];
@@ -1344,6 +1399,14 @@ static int step_box(lc_plan_t *p, int x, const lc_sources *srcs, void *const *ou
     int k = 0;
     while (k < bp.K) {
         const lc_sources &s0 = srcs[k];
+        if (point_rows(bp, s0)) {
+            int done = 0;
+            const int slot = bp.slot(k);
+            int rc = push_point_rows(p, bp, srcs + k, std::min({bp.K - k, bp.K - slot, bp.push_group}), slot, st, &done);
+            if (rc) return rc;
+            k += done;
+            continue;
+        }
         if (s0.kind != 0 || bp.spec3d) {
             // (3D spectra go through the plan's staging spectrum one slice at a time)
             int rc = push_impl(p, x, k, &s0);

@@ -43,6 +43,8 @@ hipError_t launch_x_fwd_batch(int n, bool t_f64, const SrcTab &in, int count, bo
 // 192, 256}; xy_supported): one workgroup per z-plane. Slice i reads in.p[i],
 // writes its y-transformed spectrum at spec + i*spec_stride and one FP64 sum
 // of the input per plane at dcpart + i*dc_stride + z.
+// With rows non-null the inputs are compact rows (PointTab): in.p[i] the row
+// map of slice i, rows the FP64 cells.
 // `variant` selects one of xy_variants(n) compiled launch shapes (FP64
 // input runs the first shape of the same layout).
 // Parity-layout shapes (xy_parity) take half a plane per workgroup, the rows y of one
@@ -74,13 +76,13 @@ hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const 
                          const void *part, hipStream_t st);
 hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                                const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
-                               int64_t dc_stride, int variant, hipStream_t st);
+                               int64_t dc_stride, int variant, hipStream_t st, const double *rows = nullptr);
 // The same passes in FP64 (the FP64 form; xy_supported(n)): one shape per N,
 // in the parity layout at N = 192 and 256 (plain_parity), with its inverse.
 // dcpart as for the FP32 pass.
 hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                              const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
-                             int64_t dc_stride, hipStream_t st);
+                             int64_t dc_stride, hipStream_t st, const double *rows = nullptr);
 hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
                            const void *tw_full, double scale, const double *mu, hipStream_t st);
 // Column pass over `count` spectra at spec + i*stride (complex elements).

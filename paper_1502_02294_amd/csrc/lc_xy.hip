@@ -140,18 +140,20 @@ __device__ __forceinline__ void pin(cx<float> &v) { asm volatile("" : "+v"(v.x),
 __device__ __forceinline__ void pin(cx<double> &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 __device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }
 
-template <typename T, int N, int NR_, typename TIN, bool S8, int NB_, int NC_, bool PER>
+// ROWS: the FP64 input comes as compact rows (point lists): srcs.p[slice] is
+// the slice's row map, rows the cells; an empty row is read as zeros.
+template <typename T, int N, int NR_, typename TIN, bool S8, int NB_, int NC_, bool PER, bool ROWS>
 __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_kernel(
     SrcTab srcs, cx<T> *__restrict__ spec0, int64_t spec_stride, const cx<T> *__restrict__ tw_half,
     const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double *__restrict__ dcpart,
-    int64_t dc_stride, int n_planes) {
+    int64_t dc_stride, int n_planes, const TIN *__restrict__ rows) {
     using SH = XYShape<T, N, S8, NB_, NC_, NR_>;
     constexpr int L = SH::L, TX = SH::TX, NB = SH::NB, RPB = SH::RPB, CPB = SH::CPB, NT = SH::NT;
     constexpr int NR = SH::NR, HALVES = SH::HALVES;
     constexpr int SK = SH::SK, LSX = SH::LSX, ES = SH::ES, NC = SH::NC, XS = SH::XS, RG = SH::RG;
     // input that converts exactly is summed (FP64 mean) as it is read
     constexpr bool EXIN = sizeof(TIN) <= sizeof(T);
-    static_assert(!PER || sizeof(T) == 4 && EXIN, "the persistent form reads FP32 grids");
+    static_assert(!PER || (sizeof(T) == 4 && EXIN && !ROWS), "the persistent form reads FP32 grids");
     // Row batches in flight ahead of their transform. One workgroup per
     // plane: two batches, or one of FP64 input to the FP32 form (whose loads
     // are twice as wide). Persistent workgroups: the first half of the next
@@ -176,6 +178,7 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
     const int yc = tid % CPB, yt = tid / CPB;
     const int lane = tid & 63;
     const bool t0 = xt == 0;
+    int row_slot[ROWS ? NB : 1];    // compact rows of this thread's row batches
     const int stride = gridDim.x;   // persistent form: planes w, w + stride, ... of workgroup w
 
     // row batch b of plane `pl` (row xl of the batch) into dst[b]; with
@@ -189,6 +192,21 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
             // keeps its global address space, so these stay global loads,
             // which LDS waits do not wait for)
             const int pr = pl % (N * HALVES);   // (z, parity) of plane unit pl
+            if constexpr (ROWS) {
+                const int slot = row_slot[b];
+#pragma unroll
+                for (int e = 0; e < EXN; ++e) dst[b][e] = mk((T)0, (T)0);
+                if (slot >= 0) {
+                    int64_t off = (int64_t)slot * N;
+                    if (late) asm volatile("" : "+v"(off));
+#pragma unroll
+                    for (int e = 0; e < EXN; ++e) {
+                        const cx<TIN> v = *(const cx<TIN> *)(rows + off + 2 * EX::in_pos(xt, e));
+                        dst[b][e] = mk((T)v.x, (T)v.y);
+                    }
+                }
+                return;
+            }
             int64_t off = ((int64_t)(pr / HALVES) * N + HALVES * (b * RPB + xl) + pr % HALVES) * N;
             if (late) asm volatile("" : "+v"(off));
             const TIN *row = (const TIN *)srcs.p[pl / (N * HALVES)] + off;
@@ -201,6 +219,12 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
     };
 
     int plane = blockIdx.x;
+    if constexpr (ROWS) {
+        const int pr = plane % (N * HALVES);
+        const int *map = (const int *)srcs.p[plane / (N * HALVES)] + (pr / HALVES) * N + pr % HALVES;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) row_slot[b] = map[HALVES * (b * RPB + xl)];
+    }
     cx<T> xr[NB][EXN];
     static_for<PF>([&](auto bc) { load_batch(bc, plane, xr, false); });
     // untangle twist as V_q = -i W^q / 2:  Y[q] = (A + conj B) / 2 + V_q (A - conj B)
@@ -316,10 +340,12 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
         // ---- 4. separate the packed p = 0 / p = N/2 column; FP64 plane sum
         if constexpr (!EXIN) {
             // FP64 input: the sum needs the values before rounding; read them again
-            const TIN *in = (const TIN *)srcs.p[slice] + (int64_t)z * N * N;
+            const TIN *in = ROWS ? rows : (const TIN *)srcs.p[slice] + (int64_t)z * N * N;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const TIN *row = in + (int64_t)(HALVES * (b * RPB + xl) + par) * N;
+                if (ROWS && row_slot[ROWS ? b : 0] < 0) continue;
+                const TIN *row = in + (ROWS ? (int64_t)row_slot[ROWS ? b : 0] * N
+                                            : (int64_t)(HALVES * (b * RPB + xl) + par) * N);
                 for (int e = 0; e < EXN; ++e) {
                     const cx<TIN> v = *(const cx<TIN> *)(row + 2 * EX::in_pos(xt, e));
                     dsum += (double)v.x + (double)v.y;
@@ -681,10 +707,10 @@ bool xy_parity(int n, int variant) {
     return f >= 0 && variant >= f && variant < xy_variants(n);
 }
 
-template <typename T, int N, int NR, typename TIN, bool S8, int NB, int NC, bool PER>
+template <typename T, int N, int NR, typename TIN, bool S8, int NB, int NC, bool PER, bool ROWS = false>
 static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_stride, const void *tw_half,
                        const void *twist, const void *tw_full, double *dcpart, int64_t dc_stride,
-                       hipStream_t st) {
+                       hipStream_t st, const double *rows) {
     using SH = XYShape<T, N, S8, NB, NC, NR>;
     const int n_planes = N * (N / NR) * count;
     int grid = n_planes;
@@ -696,7 +722,7 @@ static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_str
             hipDeviceProp_t prop;
             if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
                 return hipErrorInvalidDevice;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER>,
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER, ROWS>,
                                                              SH::NT, 0) != hipSuccess ||
                 per_cu < 1)
                 per_cu = 1;
@@ -704,25 +730,27 @@ static hipError_t xy_t(const SrcTab &in, int count, void *spec, int64_t spec_str
         }
         grid = std::min(grid, slots);
     }
-    hipLaunchKernelGGL((xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER>), dim3((unsigned)grid), dim3(SH::NT), 0, st, in,
+    hipLaunchKernelGGL((xy_fwd_kernel<T, N, NR, TIN, S8, NB, NC, PER, ROWS>), dim3((unsigned)grid), dim3(SH::NT), 0, st, in,
                        (cx<T> *)spec, spec_stride, (const cx<T> *)tw_half, (const cx<T> *)twist,
-                       (const cx<T> *)tw_full, dcpart, dc_stride, n_planes);
+                       (const cx<T> *)tw_full, dcpart, dc_stride, n_planes, (const TIN *)rows);
     return hipGetLastError();
 }
 
 hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                                const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
-                               int64_t dc_stride, int variant, hipStream_t st) {
+                               int64_t dc_stride, int variant, hipStream_t st, const double *rows) {
     if (count < 1 || count > SrcTab::kMax || !dcpart) return hipErrorInvalidValue;
     if (variant < 0 || variant >= xy_variants(n)) return hipErrorInvalidValue;
-    // FP64 input takes the first shape of the same spectrum layout (the
+    // FP64 input and compact rows take the first shape of the same spectrum layout (the
     // FP64-input instances of the other shapes spill)
-    if (in_f64) variant = xy_parity(n, variant) ? xy_first_parity(n) : 0;
+    if (in_f64 || rows) variant = xy_parity(n, variant) ? xy_first_parity(n) : 0;
 #define XS_(N, NR, S8, NB, NC, PER)                                                                            \
-    return in_f64 ? xy_t<float, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,       \
-                                                           tw_full, dcpart, dc_stride, st)                        \
-                  : xy_t<float, N, NR, float, S8, NB, NC, PER>(in, count, spec, spec_stride, tw_half, twist, tw_full,    \
-                                                        dcpart, dc_stride, st);
+    return rows     ? xy_t<float, N, NR, double, S8, NB, NC, false, true>(in, count, spec, spec_stride, tw_half,  \
+                                                                          twist, tw_full, dcpart, dc_stride, st, rows) \
+           : in_f64 ? xy_t<float, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,  \
+                                                                    tw_full, dcpart, dc_stride, st, nullptr)       \
+                    : xy_t<float, N, NR, float, S8, NB, NC, PER>(in, count, spec, spec_stride, tw_half, twist,     \
+                                                                 tw_full, dcpart, dc_stride, st, nullptr);
 #define X_(N, S8, NB, NC, PER) XS_(N, N, S8, NB, NC, PER)
 #define XH_(N, S8, NB, NC) XS_(N, N / 2, S8, NB, NC, false)
     switch (n) {
@@ -759,13 +787,15 @@ hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, 
 // x and y passes.
 hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                              const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
-                             int64_t dc_stride, hipStream_t st) {
+                             int64_t dc_stride, hipStream_t st, const double *rows) {
     if (count < 1 || count > SrcTab::kMax || !dcpart) return hipErrorInvalidValue;
-#define XD_(N, NR, S8, NB, NC)                                                                                  \
-    return in_f64 ? xy_t<double, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist, \
-                                                                   tw_full, dcpart, dc_stride, st)              \
-                  : xy_t<double, N, NR, float, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist,  \
-                                                                  tw_full, dcpart, dc_stride, st);
+#define XD_(N, NR, S8, NB, NC)                                                                                   \
+    return rows     ? xy_t<double, N, NR, double, S8, NB, NC, false, true>(in, count, spec, spec_stride, tw_half, \
+                                                                           twist, tw_full, dcpart, dc_stride, st, rows) \
+           : in_f64 ? xy_t<double, N, NR, double, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist, \
+                                                                     tw_full, dcpart, dc_stride, st, nullptr)     \
+                    : xy_t<double, N, NR, float, S8, NB, NC, false>(in, count, spec, spec_stride, tw_half, twist, \
+                                                                    tw_full, dcpart, dc_stride, st, nullptr);
     switch (n) {
         case 64: XD_(64, 64, false, 1, 0)
         case 96: XD_(96, 96, false, 1, 0)
