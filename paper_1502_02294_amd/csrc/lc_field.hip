@@ -18,59 +18,70 @@
 
 namespace lc {
 
-// Workgroup: 64 consecutive elements of one (tile, output, band); its four
-// waves sum a quarter of the parts each (eight loads in flight at a time)
-// and wave 0 adds the four partial sums in wave order.
+// Workgroup: 512 / Q consecutive elements of one (tile, output, band), two per
+// lane; each of its Q lane groups adds a share of the parts (eight loads in
+// flight at a time) and the first adds the Q sums in order. Q is the smallest
+// that leaves a group eight parts or fewer, up to 8: with few parts per tile
+// the reduction only adds waiting (192^3, 4 parts: Q = 1 8.9 us, Q = 4 13.6),
+// with many the loads of one group come one after another (128^3, 64 parts:
+// Q = 1 21.6 us, Q = 4 11.6). The tile and the range of its parts are the
+// same for a whole workgroup; found per element, with 64-bit divisions, they
+// cost more than the adding (192^3: 23 us).
+template <int Q>
 __global__ __launch_bounds__(256) void fused_rest_merge_kernel(RestMerge m, ColSet s0, ColSet s1) {
-    __shared__ cx<float> red[3][64];
-    const int64_t per = (int64_t)m.L * m.cpw;
-    const int64_t chunks = (per + 63) / 64;
-    const int64_t g = blockIdx.x;
-    const int64_t ch = g % chunks;
-    int64_t r = g / chunks;
-    const int b = (int)(r % m.nband);
+    constexpr int LN = 256 / Q;
+    __shared__ float4 red[Q > 1 ? Q - 1 : 1][LN];
+    const int per = m.L * m.cpw, chunks = (per + 2 * LN - 1) / (2 * LN);
+    int r = blockIdx.x;
+    const int ch = r % chunks;
+    r /= chunks;
+    const int b = r % m.nband;
     r /= m.nband;
-    const int o = (int)(r % m.no);
+    const int o = r % m.no;
     const int64_t i = r / m.no;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t e = ch * 64 + lane;
-    const bool ok_e = e < per;
+    const int lane = threadIdx.x % LN, g = threadIdx.x / LN;
+    const int e = ch * 2 * LN + 2 * lane;
     const int64_t U = m.rest * m.kmax, lo = i * m.kmax, hi = lo + m.kmax;
     // workgroups whose range starts inside the tile: w U / P in (lo, hi),
     // i.e. w in [ceil((lo + 1) P / U), ceil(hi P / U))
-    const int64_t w0 = ((lo + 1) * m.P + U - 1) / U;
-    const int64_t w1 = std::min<int64_t>(m.P, (hi * m.P + U - 1) / U);
-    const int64_t nq = (w1 - w0 + 3) / 4;
-    const int64_t qa = w0 + wv * nq, qb = std::min<int64_t>(w1, qa + nq);
-    const cx<float> *src = m.part + (int64_t)b * m.part_stride + o * per + (ok_e ? e : 0);
-    cx<float> v = mk(0.f, 0.f);
-    for (int64_t w = qa; w < qb; w += 8) {
-        cx<float> t[8];
+    const int w0 = (int)(((lo + 1) * m.P + U - 1) / U);
+    const int w1 = (int)std::min<int64_t>(m.P, (hi * m.P + U - 1) / U);
+    const int64_t tile = fused_slot_tile(m.full + i, s0.n_wgs, m.nrow, m.npb, m.gp);
+    const int nq = (w1 - w0 + Q - 1) / Q, qa = w0 + g * nq, qb = w1 < qa + nq ? w1 : qa + nq;
+    const bool ok = e < per, sparse = U < m.P;     // (sparse: some ranges are empty)
+    const cx<float> *src = m.part + (int64_t)b * m.part_stride + (int64_t)o * per + (ok ? e : 0);
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int w = qa; w < qb; w += 8) {
+        float4 t[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int64_t ww = w + j;
-            const bool on = ok_e && ww < qb && (ww + 1) * U / m.P > ww * U / m.P;   // non-empty range
-            t[j] = on ? src[m.no * ww * per] : mk(0.f, 0.f);
+            const int ww = w + j;
+            const bool on = ww < qb && (!sparse || (int64_t)(ww + 1) * U / m.P > (int64_t)ww * U / m.P);
+            t[j] = on ? *(const float4 *)(src + (int64_t)m.no * ww * per) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v = v + t[j];
+        for (int j = 0; j < 8; ++j) v = make_float4(v.x + t[j].x, v.y + t[j].y, v.z + t[j].z, v.w + t[j].w);
     }
-    if (wv > 0) red[wv - 1][lane] = v;
-    __syncthreads();
-    if (wv > 0 || !ok_e) return;
-    v = v + red[0][lane];
-    v = v + red[1][lane];
-    v = v + red[2][lane];
-    const int z = (int)(e / m.cpw), c = (int)(e % m.cpw);
-    const int64_t tile = fused_slot_tile(m.full + i, s0.n_wgs, m.nrow, m.npb, m.gp);
+    if constexpr (Q > 1) {
+        if (g > 0) red[g - 1][lane] = v;
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int q = 0; q < Q - 1; ++q) {
+            const float4 u = red[q][lane];
+            v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
+        }
+    }
+    if (!ok) return;
     const bool is_main = tile < s0.n_wgs;
     const ColSet &s = is_main ? s0 : s1;
+    const int z = e / m.cpw, c = e % m.cpw;
     const int64_t col = (is_main ? tile : tile - s0.n_wgs) * m.cpw + c;
-    if (col >= s.n_cols) return;
     const int64_t H = m.L / 2;
     const int64_t obase = is_main ? H * H : H;
     cx<float> *dst = m.acc + (int64_t)b * m.acc_stride + o * obase + col_base(s, col) + (int64_t)z * s.row_stride;
-    *dst = *dst + v;
+    if (col < s.n_cols) dst[0] = dst[0] + mk(v.x, v.y);
+    if (col + 1 < s.n_cols) dst[1] = dst[1] + mk(v.z, v.w);
 }
 
 // tab[t] = the workgroup holding the second part of tile t, or -1. With
@@ -101,8 +112,14 @@ __global__ __launch_bounds__(256) void fused_split_kernel(int *__restrict__ tab,
 }
 
 void launch_fused_rest_merge(const RestMerge &m, const ColSet &s0, const ColSet &s1, hipStream_t st) {
-    const int64_t wgs = m.rest * m.no * m.nband * (((int64_t)m.L * m.cpw + 63) / 64);
-    hipLaunchKernelGGL(fused_rest_merge_kernel, dim3((unsigned)wgs), dim3(256), 0, st, m, s0, s1);
+    const int64_t parts = (m.P + m.rest - 1) / m.rest, per = (int64_t)m.L * m.cpw;   // parts per tile, its elements
+#define RM_(Q)                                                                                                     \
+    hipLaunchKernelGGL(fused_rest_merge_kernel<Q>, dim3((unsigned)(m.rest * m.no * m.nband * ((per * Q + 511) / 512))), \
+                       dim3(256), 0, st, m, s0, s1)
+    if (parts <= 8) RM_(1);
+    else if (parts <= 32) RM_(4);
+    else RM_(8);
+#undef RM_
 }
 
 void launch_fused_split(int *tab, int64_t tiles, int64_t kmax, int64_t P, int64_t W, int32_t pair, int64_t main_k,
@@ -125,7 +142,10 @@ int fused_max_bands(int n) { return (n == 384 || n == 512) ? 4 : 2; }
 
 // Built-in choice: prefetch depth 2 for one band per launch, 1 for two (the
 // two-band instances of depth 2 spill registers).
+// (N = 128: 1 for both, whose third workgroup per CU is worth more: one band
+// of 24 slices 54.7 us against 60.0.)
 int fused_default_variant(int n, int nband) {
+    if (n == 128) return 3;
     if (n == 384) return 1;   // depth 1 is the instance without spills there
     const int s8 = fused_variants(n) > 2 ? 2 : 0;
     return s8 + (nband > 1 ? 1 : 0);
@@ -161,20 +181,18 @@ hipError_t launch_fused_plain(int n, bool t_f64, const FusedArgs &a, const void 
 __global__ __launch_bounds__(256) void dc_slice_kernel(const double *__restrict__ dcpart, int W,
                                                        double *__restrict__ sk, int *__restrict__ status,
                                                        int ring, int K) {
-    __shared__ double red[256];
+    __shared__ double red[4];
     const int k = blockIdx.x;
     double s = 0.0;
     for (int w = threadIdx.x; w < W; w += 256) s += dcpart[(int64_t)k * W + w];
-    red[threadIdx.x] = s;
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        sk[k] = red[0];
+        s = red[0] + red[1] + red[2] + red[3];
+        sk[k] = s;
         // a NaN or infinite source value makes its slice's FP64 sum non-finite
-        if (status && !isfinite(red[0])) {
+        if (status && !isfinite(s)) {
             atomicAdd(&status[0], 1);
             atomicMin(&status[1], k >= ring ? k - ring : k - ring + K);
         }

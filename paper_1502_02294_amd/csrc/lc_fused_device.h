@@ -529,8 +529,8 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
 // w U / P <= u < (w + 1) U / P, U = rest kmax. The workgroup whose range holds
 // unit i kmax wrote tile i to the accumulator; every other workgroup whose
 // range starts inside tile i left its part in slot NO w + o (output o).
-// The parts are added in a fixed order (within each quarter of the range in
-// workgroup order, then the quarters in order), so the result does not
+// The parts are added in a fixed order (within each share of the range in
+// workgroup order, then the shares in order), so the result does not
 // depend on timing.
 struct RestMerge {
     cx<float> *acc;
