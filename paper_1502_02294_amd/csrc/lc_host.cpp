@@ -263,7 +263,7 @@ struct BoxPlan {
     // part of the schedule), in the parity layout at N = 192 and 256
     bool plain = false;
     bool plain_xy() const { return plain && xy_supported(n); }
-    bool plain_parity() const { return plain_xy() && yx_inv_supported(n); }
+    bool plain_parity() const { return plain_xy() && yx_inv_supported(n, true); }
     int dc_width() const { return use_xy ? (parity() ? 2 : 1) * n : xwgs; }
     int64_t dc_cap() const { return std::max<int64_t>(2 * (int64_t)n, xwgs); }   // dcpart entries per slice
 };
@@ -487,6 +487,25 @@ hipError_t inv_y_fused(int n, void *acc, const void *tw_full, const int *tab, co
                   : launch_col_y_inv_combine(n, acc, tw_full, tab, part, st);
 }
 
+// Inverse y + x pass of bands [b, b + nb) with the fused pass's schedule (the
+// stream-K mode's split tiles are merged while loading).
+InvArgs inv_args(const BoxPlan &bp, size_t cs, int b, int nb, bool parity) {
+    InvArgs a{};
+    a.acc_stride = spec_elems(bp.n);
+    a.acc = bp.acc + (size_t)b * a.acc_stride * cs;
+    a.nband = nb;
+    a.parity = parity;
+    a.tw_half = bp.tw_half; a.twist = bp.twist; a.tw_full = bp.tw_full;
+    a.scale = 1.0 / ((double)bp.n * bp.n * bp.n);
+    a.mu = bp.mu + b;
+    if (!bp.plain && !bp.fused_rounds) {
+        a.split_tab = bp.split_tab + (size_t)(b / bp.fused_bands) * bp.tiles;
+        a.part = bp.part;
+        a.part_stride = bp.part_stride;
+    }
+    return a;
+}
+
 FusedArgs fused_args(const BoxPlan &bp) {
     FusedArgs fa;
     const int n = bp.n;
@@ -625,9 +644,11 @@ int autotune_box_uncached(lc_plan_t *p, BoxPlan &bp) {
                 int rc = time_calls(p->stream, 2, [&]() {
                     hipError_t e = launch_fused_z(n, fa, bp.tw_full, p->stream);
                     if (e != hipSuccess) return e;
-                    if (lay)
-                        return launch_yx_inv(n, bp.acc, p->scratch_real, false, bp.tw_half, bp.twist, bp.tw_full,
-                                             1.0, bp.mu, bp.split_tab, r ? nullptr : bp.part, p->stream);
+                    if (yx_inv_supported(n, lay == 1)) {
+                        InvArgs ia = inv_args(bp, 8, 0, 1, lay == 1);
+                        ia.out[0] = p->scratch_real;
+                        return launch_yx_inv(n, false, ia, p->stream);
+                    }
                     e = inv_y_fused(n, bp.acc, bp.tw_full, bp.split_tab, bp.part, r != 0, p->stream);
                     if (e != hipSuccess) return e;
                     return launch_x_inv(n, false, bp.acc, p->scratch_real, false, bp.tw_half, bp.twist, 1.0, nullptr,
@@ -1191,15 +1212,17 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
             fa.frozen = frozen;
             fa.sk = bp.sk; fa.g0 = bp.ghat0; fa.inv_n3 = inv_n3; fa.mu = bp.mu;
             HIPCHK(launch_fused_z(n, fa, bp.tw_full, st));
+            if (yx_inv_supported(n, bp.parity())) {
+                InvArgs ia = inv_args(bp, cs, b, nb, bp.parity());
+                ia.out_f64 = out_f64;
+                for (int j = 0; j < nb; ++j) ia.out[j] = outp[b + j - b0];
+                HIPCHK(launch_yx_inv(n, false, ia, st));
+                b += nb;
+                continue;
+            }
             for (int j = 0; j < nb; ++j) {
                 char *acc = bp.acc + (size_t)(b + j) * se * cs;
                 char *part = bp.part + (size_t)j * bp.part_stride * 8;
-                if (fa.parity) {
-                    // parity-layout accumulator: inverse y + x fused per half plane
-                    HIPCHK(launch_yx_inv(n, acc, outp[b + j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
-                                         inv_n3, bp.mu + b + j, tab, fa.rounds ? nullptr : part, st));
-                    continue;
-                }
                 HIPCHK(inv_y_fused(n, acc, bp.tw_full, tab, part, fa.rounds != 0, st));
                 HIPCHK(launch_x_inv(n, false, acc, outp[b + j - b0], out_f64, bp.tw_half, bp.twist, inv_n3,
                                     bp.mu + b + j, st));
@@ -1210,15 +1233,16 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
         for (int b = b0; b < b1;) {
             const int nb = std::min(kPlainBands, b1 - b);
             HIPCHK(launch_fused_plain(n, p->t_f64, plain_args(p, bp, b, nb, frozen), bp.tw_full, st));
+            if (yx_inv_supported(n, bp.plain_parity())) {
+                InvArgs ia = inv_args(bp, cs, b, nb, bp.plain_parity());
+                ia.out_f64 = out_f64;
+                for (int j = 0; j < nb; ++j) ia.out[j] = outp[b + j - b0];
+                HIPCHK(launch_yx_inv(n, p->t_f64, ia, st));
+                b += nb;
+                continue;
+            }
             for (int j = b; j < b + nb; ++j) {
                 char *acc = bp.acc + (size_t)j * se * cs;
-                if (bp.plain_parity()) {
-                    HIPCHK(p->t_f64 ? launch_yx64_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
-                                                      inv_n3, bp.mu + j, st)
-                                    : launch_yx_inv(n, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, bp.tw_full,
-                                                    inv_n3, bp.mu + j, nullptr, nullptr, st));
-                    continue;
-                }
                 HIPCHK(launch_col(n, p->t_f64, 1, false, acc, bp.tw_full, st));
                 HIPCHK(launch_x_inv(n, p->t_f64, acc, outp[j - b0], out_f64, bp.tw_half, bp.twist, inv_n3, nullptr,
                                     st));
@@ -1637,9 +1661,11 @@ int lc_time_kernel(lc_plan_t *p, int32_t box, int32_t kernel, int32_t reps, doub
             case LC_KERNEL_COL_Y_INV:
                 return fused ? inv_y_fused(n, acc0, bp.tw_full, bp.split_tab, bp.part, bp.fused_rounds != 0, st)
                              : launch_col(n, p->t_f64, 1, false, acc0, bp.tw_full, st);
-            case LC_KERNEL_YX_INV:
-                return launch_yx_inv(n, acc0, p->scratch_real, false, bp.tw_half, bp.twist, bp.tw_full,
-                                     1.0 / (double)n3, bp.mu, bp.split_tab, bp.fused_rounds ? nullptr : bp.part, st);
+            case LC_KERNEL_YX_INV: {
+                InvArgs ia = inv_args(bp, cs, 0, 1, true);
+                ia.out[0] = p->scratch_real;
+                return launch_yx_inv(n, false, ia, st);
+            }
             default:
                 return launch_x_inv(n, p->t_f64, acc0, p->scratch_real, p->t_f64, bp.tw_half, bp.twist,
                                     1.0 / (double)n3, fused ? bp.mu : nullptr, st);

@@ -65,26 +65,38 @@ bool xy_supported(int n);
 int xy_variants(int n);
 bool xy_parity(int n, int variant);
 int xy_first_parity(int n);   // first parity-layout shape, -1 if none
-// Inverse y + x passes and epilogue of one band's FP32 accumulator in the
-// parity layout left by the fused z pass with parity input (rows q and
-// N/2 + q hold U_0 = T[q] + T[q+N/2] and U_1 = W_N^-q (T[q] - T[q+N/2])):
-// out = IDFT(acc) * scale + *mu, N^3 reals (FP32 or FP64). With part
-// non-null the second parts of split fused tiles (split_tab) are added.
-bool yx_inv_supported(int n);
-hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                         const void *tw_full, double scale, const double *mu, const int *split_tab,
-                         const void *part, hipStream_t st);
+// Inverse y + x passes and epilogue of the bands of one fused launch, FP32 or
+// FP64 accumulators: in the parity layout left by the fused z pass with parity
+// input (rows q and N/2 + q hold U_0 = T[q] + T[q+N/2] and
+// U_1 = W_N^-q (T[q] - T[q+N/2]); N = 192, 256), or whole planes (N = 64, 96,
+// 128): out[b] = IDFT(acc + b acc_stride) * scale + mu[b], N^3 reals (FP32 or
+// FP64). With part non-null (FP32) the second parts of split fused tiles
+// (split_tab) are added.
+struct InvArgs {
+    static constexpr int kMax = 4;
+    const void *acc;
+    int64_t acc_stride;       // complex elements
+    int32_t nband;
+    bool parity, out_f64;
+    void *out[kMax];
+    const void *tw_half, *twist, *tw_full;
+    double scale;
+    const double *mu;
+    const int *split_tab;
+    const void *part;
+    int64_t part_stride;      // complex elements, per band
+};
+bool yx_inv_supported(int n, bool parity);
+hipError_t launch_yx_inv(int n, bool t_f64, const InvArgs &a, hipStream_t st);
 hipError_t launch_xy_fwd_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                                const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
                                int64_t dc_stride, int variant, hipStream_t st, const double *rows = nullptr);
 // The same passes in FP64 (the FP64 form; xy_supported(n)): one shape per N,
-// in the parity layout at N = 192 and 256 (plain_parity), with its inverse.
+// in the parity layout at N = 192 and 256.
 // dcpart as for the FP32 pass.
 hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, void *spec, int64_t spec_stride,
                              const void *tw_half, const void *twist, const void *tw_full, double *dcpart,
                              int64_t dc_stride, hipStream_t st, const double *rows = nullptr);
-hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                           const void *tw_full, double scale, const double *mu, hipStream_t st);
 // Column pass over `count` spectra at spec + i*stride (complex elements).
 hipError_t launch_col_batch(int n, bool t_f64, int axis, bool fwd, void *spec, int64_t stride, int count,
                             const void *tw_full, hipStream_t st);

@@ -57,6 +57,11 @@ template <int C, int I = 0, typename F> __device__ __forceinline__ void static_f
 __device__ __forceinline__ float fma_(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return fma(a, b, c); }
 
+// Output pointers of the bands of one inverse launch (by value).
+struct OutTab {
+    void *p[InvArgs::kMax];
+};
+
 // Launch shape: S8 selects the 8-elements-per-thread schedules (smaller
 // register working set, one more LDS exchange per line), NB_ the number of
 // row batches of the x phase (= column batches of the y phase), NC_ the
@@ -380,30 +385,34 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
 }
 
 // Inverse y and x passes and the epilogue of Eq. 12's inverse transform,
-// fused per half z-plane, for an FP32 accumulator in the parity layout (the
-// fused z pass with parity input leaves, in rows q and N/2 + q of every
-// z-plane, U_0 = T[q] + T[q + N/2] and U_1 = W_N^-q (T[q] - T[q + N/2])).
-// Output rows y = 2m + s of one z-plane are the N/2-point inverse y
-// transform of U_s, so a workgroup takes (z, s), reads its half plane once
-// and writes N/2 output rows once:
-//   1. column batch by column batch (lanes walk the columns), the N/2-point
-//      inverse y transform in registers; the p = 0 and p = N/2 columns, whose
-//      inverse transforms are real, travel packed as U_s[.][0] + i U_s[.][N/2];
+// fused per z-plane (N <= 128), or per half plane for an accumulator in the
+// parity layout (the fused z pass with parity input leaves, in rows q and
+// N/2 + q of every z-plane, U_0 = T[q] + T[q + N/2] and
+// U_1 = W_N^-q (T[q] - T[q + N/2])). Output rows y = 2m + s of one z-plane are
+// the N/2-point inverse y transform of U_s (whole planes: all rows, the
+// N-point transform of T), so a workgroup takes (z, s) of one band, reads its
+// (half) plane once and writes its output rows once; one launch takes the
+// bands of a fused launch:
+//   1. column batch by column batch (lanes walk the columns), the inverse
+//      y transform in registers; the p = 0 and p = N/2 columns, whose inverse
+//      transforms are real, travel packed as U_s[.][0] + i U_s[.][N/2];
 //   2. row batch by row batch, the rows are transposed through LDS and each
 //      goes through the complex-to-real x transform (the retangle
 //      Z[p] = E'_p + i O'_p of the half-length trick, then the N/2-point
 //      inverse transform), scaled by 1/N^3, plus the FP64 mean, and stored.
 // With COMBINE the second parts of tiles that the fused pass split between
 // two workgroups (tab, part) are added while loading.
-template <typename T, int N, typename TOUT, bool S8, int NB_, bool COMBINE>
-__global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv_kernel(
-    const cx<T> *__restrict__ acc, TOUT *__restrict__ out, const cx<T> *__restrict__ tw_half,
-    const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double scale,
-    const double *__restrict__ mu, const int *__restrict__ tab, const cx<T> *__restrict__ part, int cpw_z,
+// At 128^3 the separate passes took 7.2 + 8.4 us a band, this one 12.1 us;
+// two bands of 96^3 22 us in four launches, 11.8 us in one.
+template <typename T, int N, int NR_, typename TOUT, bool S8, int NB_, bool COMBINE>
+__global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, NR_>::NT)) void yx_inv_kernel(
+    const cx<T> *__restrict__ acc0, int64_t acc_stride, OutTab outs, const cx<T> *__restrict__ tw_half,
+    const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double scale, const double *__restrict__ mu,
+    const int *__restrict__ tab, const cx<T> *__restrict__ part0, int64_t part_stride, int cpw_z,
     int64_t tiles_main) {
-    using SH = XYShape<T, N, S8, NB_, 0, N / 2>;
+    using SH = XYShape<T, N, S8, NB_, 0, NR_>;
     constexpr int L = SH::L, NR = SH::NR, TX = SH::TX, TY = SH::TY, NB = SH::NB, RPB = SH::RPB, CPB = SH::CPB;
-    constexpr int NT = SH::NT, SK = SH::SK, LSX = SH::LSX;
+    constexpr int NT = SH::NT, SK = SH::SK, LSX = SH::LSX, HALVES = SH::HALVES;
     using EY = Engine<T, NR, false, typename SH::SY>;
     using EX = Engine<T, L, false, typename SH::SX, SK>;
     constexpr int EYN = EY::E, EXN = EX::E;
@@ -421,7 +430,10 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
     const int tid = threadIdx.x;
     const int yc = tid % CPB, yt = tid / CPB;
     const int xl = tid / TX, xt = tid % TX;
-    const int z = blockIdx.x / 2, sp = blockIdx.x % 2;
+    const int band = blockIdx.x / (N * HALVES), z = blockIdx.x % (N * HALVES) / HALVES, sp = blockIdx.x % HALVES;
+    const cx<T> *__restrict__ acc = acc0 + band * acc_stride;
+    const cx<T> *__restrict__ part = part0 + band * part_stride;
+    TOUT *__restrict__ out = (TOUT *)outs.p[band];
     const cx<T> *__restrict__ mainp = acc + ((int64_t)z * N + sp * NR) * L;
     const cx<T> *__restrict__ nyq = acc + spec_main(N) + (int64_t)z * N + sp * NR;
 
@@ -460,7 +472,7 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
         twx[i] = tw_half[i];
         twt[i] = twist[i];
     }
-    for (int i = tid; i < NR; i += NT) twy[i] = tw_full[2 * i];   // W_NR^i = W_N^(2i)
+    for (int i = tid; i < NR; i += NT) twy[i] = tw_full[HALVES * i];   // W_NR^i = W_N^(HALVES i)
     lds_barrier();
 
     // ---- 1. inverse y transforms, one column batch at a time (in place)
@@ -470,7 +482,7 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
     });
 
     // ---- 2. per row batch: transpose, C2R x transform, epilogue
-    const double m = *mu;
+    const double m = mu[band];
     cx<T> *rreg = lds, *xreg = lds + RREG;
     static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
@@ -504,7 +516,7 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
             }
         }
         EX::run(zx, xreg, xl * LSX, 1, xt, twx);
-        const int y = 2 * (rb * RPB + xl) + sp;
+        const int y = HALVES * (rb * RPB + xl) + sp;
         TOUT *orow = out + ((int64_t)z * N + y) * N;
 #pragma unroll
         for (int e = 0; e < EXN; ++e) {
@@ -516,38 +528,47 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, N / 2>::NT)) void yx_inv
     });
 }
 
-bool yx_inv_supported(int n) { return n == 192 || n == 256; }
+bool yx_inv_supported(int n, bool parity) {
+    return parity ? n == 192 || n == 256 : n == 64 || n == 96 || n == 128;
+}
 
-template <int N>
-static hipError_t yx_inv_t(const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                           const void *tw_full, double scale, const double *mu, const int *split_tab,
-                           const void *part, hipStream_t st) {
-    constexpr bool S8 = false;
-    constexpr int NB = 4;
-    using SH = XYShape<float, N, S8, NB, 0, N / 2>;
+template <typename T, int N, int NR, bool S8, int NB>
+static hipError_t yx_inv_t(const InvArgs &a, hipStream_t st) {
+    using SH = XYShape<T, N, S8, NB, 0, NR>;
     const int cpw = fused_cpw(N);
     const int64_t tiles_main = (int64_t)N * (N / 2) / cpw;
-    const dim3 grid(2 * N);
-#define YI_(TOUT, COMB)                                                                                       \
-    hipLaunchKernelGGL((yx_inv_kernel<float, N, TOUT, S8, NB, COMB>), grid, dim3(SH::NT), 0, st, (const cx<float> *)acc, \
-                       (TOUT *)out, (const cx<float> *)tw_half, (const cx<float> *)twist,                       \
-                       (const cx<float> *)tw_full, scale, mu, split_tab, (const cx<float> *)part, cpw, tiles_main)
-    if (part) {
-        if (out_f64) YI_(double, true); else YI_(float, true);
-    } else {
-        if (out_f64) YI_(double, false); else YI_(float, false);
+    const dim3 grid((unsigned)(N * (N / NR) * a.nband));
+    OutTab outs;
+    for (int b = 0; b < a.nband; ++b) outs.p[b] = a.out[b];
+#define YI_(TOUT, COMB)                                                                                            \
+    hipLaunchKernelGGL((yx_inv_kernel<T, N, NR, TOUT, S8, NB, COMB>), grid, dim3(SH::NT), 0, st,                   \
+                       (const cx<T> *)a.acc, a.acc_stride, outs, (const cx<T> *)a.tw_half, (const cx<T> *)a.twist, \
+                       (const cx<T> *)a.tw_full, a.scale, a.mu, a.split_tab, (const cx<T> *)a.part, a.part_stride, \
+                       cpw, tiles_main)
+    if constexpr (sizeof(T) == 4) {
+        if (a.part) {
+            if (a.out_f64) YI_(double, true); else YI_(float, true);
+            return hipGetLastError();
+        }
     }
+    if (a.out_f64) YI_(double, false); else YI_(float, false);
 #undef YI_
     return hipGetLastError();
 }
 
-hipError_t launch_yx_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                         const void *tw_full, double scale, const double *mu, const int *split_tab,
-                         const void *part, hipStream_t st) {
-    if (!mu) return hipErrorInvalidValue;
-    if (n == 256) return yx_inv_t<256>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
-    if (n == 192) return yx_inv_t<192>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, split_tab, part, st);
-    return hipErrorInvalidValue;
+hipError_t launch_yx_inv(int n, bool t_f64, const InvArgs &a, hipStream_t st) {
+    if (!a.mu || a.nband < 1 || a.nband > InvArgs::kMax || (t_f64 && a.part) || !yx_inv_supported(n, a.parity))
+        return hipErrorInvalidValue;
+#define Y_(N, NR, S8, NB) return t_f64 ? yx_inv_t<double, N, NR, S8, NB>(a, st) : yx_inv_t<float, N, NR, S8, NB>(a, st);
+    switch (n) {
+        case 64: Y_(64, 64, false, 1)
+        case 96: Y_(96, 96, false, 1)
+        case 128: Y_(128, 128, true, 2)
+        case 192: return t_f64 ? yx_inv_t<double, 192, 96, false, 2>(a, st) : yx_inv_t<float, 192, 96, false, 4>(a, st);
+        case 256: return t_f64 ? yx_inv_t<double, 256, 128, true, 4>(a, st) : yx_inv_t<float, 256, 128, false, 4>(a, st);
+        default: return hipErrorInvalidValue;
+    }
+#undef Y_
 }
 
 // Forward x pass alone, FP32 spectrum, for N = 512 (a z-plane is too large
@@ -805,28 +826,6 @@ hipError_t launch_xy64_batch(int n, const SrcTab &in, int count, bool in_f64, vo
         default: return hipErrorInvalidValue;
     }
 #undef XD_
-}
-
-template <int N, bool S8, int NB>
-static hipError_t yx64_t(const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                         const void *tw_full, double scale, const double *mu, hipStream_t st) {
-    using SH = XYShape<double, N, S8, NB, 0, N / 2>;
-#define YD_(TOUT)                                                                                                   \
-    hipLaunchKernelGGL((yx_inv_kernel<double, N, TOUT, S8, NB, false>), dim3(2 * N), dim3(SH::NT), 0, st,            \
-                       (const cx<double> *)acc, (TOUT *)out, (const cx<double> *)tw_half, (const cx<double> *)twist, \
-                       (const cx<double> *)tw_full, scale, mu, nullptr, (const cx<double> *)nullptr, 1, (int64_t)0)
-    if (out_f64) YD_(double);
-    else YD_(float);
-#undef YD_
-    return hipGetLastError();
-}
-
-hipError_t launch_yx64_inv(int n, const void *acc, void *out, bool out_f64, const void *tw_half, const void *twist,
-                           const void *tw_full, double scale, const double *mu, hipStream_t st) {
-    if (!mu) return hipErrorInvalidValue;
-    if (n == 256) return yx64_t<256, true, 4>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, st);
-    if (n == 192) return yx64_t<192, false, 2>(acc, out, out_f64, tw_half, twist, tw_full, scale, mu, st);
-    return hipErrorInvalidValue;
 }
 
 }  // namespace lc
