@@ -226,8 +226,9 @@ int lc_field(lc_plan_t *plan, int32_t box, int32_t band, void *const *out,
  * band: push all slices from srcs (box-major, lookback order,
  * sum_b K_b entries, device memory only) and evaluate every band into out
  * (box-major, band, device memory). With use_graph = 1 the launch sequence
- * is captured in a HIP graph on first use and replayed while the argument
- * pointers are unchanged. With dense sources only, the boxes of a
+ * of a plan of several boxes is captured in a HIP graph on first use and
+ * replayed while the argument pointers are unchanged; the few launches of a
+ * single box are enqueued directly, which takes less time than a replay. With dense sources only, the boxes of a
  * multi-box plan run concurrently on the plan's stream and its side
  * streams, forked from and joined back to the plan's stream: as for every
  * call, the work is complete when the plan's stream reaches the end of the
