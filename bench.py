@@ -7,7 +7,7 @@ field of every band is evaluated (lc_step, replayed from a captured HIP
 graph). Kernel construction is precomputation and is timed separately.
 
 Prints ONE JSON line. Headline workload: 256^3 grid, 200 Mpc box, 40 slices
-of 5 Mpc, FP32 form (Kahan slice sum, FP64 mean and kernels); the plain FP64
+of 5 Mpc, FP32 form (FP64 slice sum, mean and kernels); the plain FP64
 method is timed at the same shape for comparison. Beside the headline the
 line carries the 512^3 x 60 x 4-band step, the 16 uneven boxes in one step,
 and the rolling light-cone (one new slice per observing time).
@@ -593,7 +593,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": f"{w.name}: {desc}", "grid": n, "slices": K, "bands": B,
-                   "form": "FP32 butterflies, Kahan slice sum, FP64 twiddles/kernels/mean",
+                   "form": "FP32 butterflies, FP64 slice sum, twiddles, kernels and mean",
                    "input": "dense FP32 source grids resident in HBM", "graph": True,
                    "schedule": r32["schedule"]},
     }

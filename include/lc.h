@@ -74,8 +74,9 @@ typedef enum {
      * same unfused passes as LC_PREC_FP64. */
     LC_PREC_FP32_PLAIN = 1,
     /* FP32 butterflies with twiddles generated in FP64; the forward z
-     * transform, the multiply-accumulate over slices (compensated,
-     * Kahan) and the inverse z transform fused in one pass; the mean
+     * transform, the multiply-accumulate over slices (summed in FP64 with
+     * one or two bands per launch) and the inverse z transform fused in
+     * one pass; the mean
      * (DC) mode summed in FP64 and added back in FP64; kernels built in
      * FP64 and stored in FP32. */
     LC_PREC_FP32 = 2
@@ -394,8 +395,8 @@ typedef enum {
  *   fused_bands    bands that one fused z launch takes (each launch reads
  *                  the slice spectra once), 1..n_fused_bands (FP32 form; -1
  *                  in the other forms). With 1 or 2 the sum over slices is
- *                  compensated (Kahan); with 3 or 4 (N = 384, 512) it is a
- *                  plain FP32 sum. Default n_fused_bands; not tuned.
+ *                  in FP64; with 3 or 4 (N = 384, 512) it is a plain
+ *                  FP32 sum. Default n_fused_bands; not tuned.
  *   spectra_3d     1: the slice spectra are stored transformed along z as
  *                  well (3D spectra, as in the plain forms): each push adds
  *                  the z pass, and a field is the product with G^ and the

@@ -6,7 +6,7 @@
 //
 // fused_z (lc_fused_device.h): per column of the y-transformed slices, the
 // forward z transform of each slice, the multiply by G^ and the sum over
-// slices (compensated, Kahan, in the FP32 form) are done in registers; the
+// slices (in FP64 in the FP32 form) are done in registers; the
 // inverse z transform follows and A is written once. Slices left in the
 // parity y layout by the half-plane xy pass get their last y radix-2 step on
 // the way in, two output columns per input column. The plain forms (FP64,
@@ -131,10 +131,8 @@ void launch_fused_split(int *tab, int64_t tiles, int64_t kmax, int64_t P, int64_
 // variants: bit 0 selects a prefetch depth of 1 (else 2) slices (fewer
 // registers: the two-band instances need it), bit 1 the eight-element
 // schedule where one exists (N = 384, 512: the eight-element schedule only,
-// bit 0 alone)
-int fused_variants(int n) {
-    return (n == 384 || n == 512) ? 2 : (n == 64 || n == 128 || n == 192 || n == 256) ? 4 : 2;
-}
+// bit 0 alone). At N = 128 and 256 the last variant is the lane-exchange kernel.
+int fused_variants(int n) { return n == 128 || n == 256 ? 5 : n == 64 || n == 192 ? 4 : 2; }
 
 bool fused_parity_supported(int n) { return n == 192 || n == 256; }
 
@@ -142,10 +140,11 @@ int fused_max_bands(int n) { return (n == 384 || n == 512) ? 4 : 2; }
 
 // Built-in choice: prefetch depth 2 for one band per launch, 1 for two (the
 // two-band instances of depth 2 spill registers).
-// (N = 128: 1 for both, whose third workgroup per CU is worth more: one band
-// of 24 slices 54.7 us against 60.0.)
+// (N = 128 and 256: the lane-exchange kernel; two bands at 128 the
+// eight-element schedule of depth 1, 68.5 us for 24 slices against 71.)
 int fused_default_variant(int n, int nband) {
-    if (n == 128) return 3;
+    if (n == 256) return 4;
+    if (n == 128) return nband > 1 ? 3 : 4;
     if (n == 384) return 1;   // depth 1 is the instance without spills there
     const int s8 = fused_variants(n) > 2 ? 2 : 0;
     return s8 + (nband > 1 ? 1 : 0);

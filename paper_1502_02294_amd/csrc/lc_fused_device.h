@@ -66,7 +66,9 @@ __host__ __device__ constexpr int fused_gp(int cpw, int tsize) {
 // one XCD (workgroups are dispatched to the 8 XCDs in turn), so slot s of
 // a block of 16*GP consecutive slots takes member (s % (16 GP)) / 8 of
 // group 8 * (s / (16 GP)) + s % 8: the readers of a line are resident
-// together on one XCD and it comes from that XCD's L2 once. Other tile
+// together on one XCD and it comes from that XCD's L2 once. The p-blocks
+// rotate by row, or one XCD would read the same 256 bytes of every row
+// (256^3: 741 us against 757; 192^3: 177 against 182). Other tile
 // counts, and tiles that do not split rows evenly (npb = 0), keep the
 // identity order; the result is always a main tile when slot is one.
 // With spectra in the parity layout, a tile covers rows q and q + N/2
@@ -81,10 +83,50 @@ __device__ __forceinline__ int64_t fused_slot_tile(int64_t slot, int64_t main_ti
     const int xcd = (int)(slot & 7), j = (int)((slot % bs) >> 3);
     const int64_t g = blk * 8 + xcd;
     const int ngp = npb / gp;
-    const int q = (int)(g / ngp), pb = gp * (int)(g % ngp) + (j % gp);
+    const int q = (int)(g / ngp), pb = gp * (int)((g + q) % ngp) + (j % gp);
     const int row = j < gp ? q : (q == 0 ? n / 2 : n - q);
     const int64_t tile = (int64_t)row * npb + pb;
     return tile < main_tiles ? tile : slot;
+}
+
+// The tiles and slices of workgroup w, as segment(tile, first slice, end).
+template <int L, int CPW, bool PAR, typename T, typename F>
+__device__ __forceinline__ void fused_walk(const FusedDev<T> &a, const ColSet &s0, int w, F &&segment) {
+    if (a.rounds) {
+        // whole tiles in rounds: all workgroups sweep the slices together
+        // main tiles per row (0: rows do not split into whole tiles, identity order)
+        const int npb = (L / 2) % CPW == 0 ? (int)((L / 2) / CPW) : 0;
+        constexpr int GP = fused_gp(CPW, sizeof(T));
+        const int nrow = PAR ? L / 2 : L;
+        const int64_t full = a.tiles / a.P * a.P;   // slots of the whole rounds
+        for (int64_t slot = w; slot < full; slot += a.P)
+            segment(fused_slot_tile(slot, s0.n_wgs, nrow, npb, GP), 0, a.kmax);
+        // the tiles of the remaining slots (fewer than P) would leave most
+        // workgroups idle for a whole round: their (tile, slice) pairs are
+        // split evenly over all workgroups instead. Only a workgroup's first
+        // segment can start inside a tile; it goes to the workgroup's part
+        // slot, and fused_rest_merge_kernel adds the parts of each tile.
+        const int64_t U = (a.tiles - full) * a.kmax;
+        int64_t u = (int64_t)w * U / a.P;
+        const int64_t ue = (int64_t)(w + 1) * U / a.P;
+        while (u < ue) {
+            const int64_t i = u / a.kmax;
+            const int k0 = (int)(u % a.kmax);
+            const int k1 = (int)std::min<int64_t>(a.kmax, k0 + (ue - u));
+            u += k1 - k0;
+            segment(fused_slot_tile(full + i, s0.n_wgs, nrow, npb, GP), k0, k1);
+        }
+    } else {
+        int64_t pos = (int64_t)w * a.W / a.P;
+        const int64_t end = (int64_t)(w + 1) * a.W / a.P;
+        while (pos < end) {
+            const int64_t tile = pos / a.kmax;
+            const int k0 = (int)(pos % a.kmax);
+            const int k1 = (int)std::min<int64_t>(a.kmax, k0 + (end - pos));
+            pos += k1 - k0;
+            segment(tile, k0, k1);
+        }
+    }
 }
 
 // PAR: the slice spectra are in the parity layout of the half-plane xy
@@ -94,12 +136,15 @@ __device__ __forceinline__ int64_t fused_slot_tile(int64_t slot, int64_t main_ti
 //   T[q] = E + W_N^q O,   T[q + N/2] = E - W_N^q O
 // (its last radix-2 step), formed on the way to the first butterfly: each
 // input element is read once for both, and both go through the z transform,
-// the kernel product and the compensated sum. Output o of a column is at
+// the kernel product and the sum. Output o of a column is at
 // o * (N/2 rows) after the first; a second part goes to part slot 2 w + o.
-// KS: compensated (Kahan) sums (the FP32 form with one or two bands per
-// launch; four bands per launch keep plain FP32 sums: their compensation terms
-// would not fit in registers beside the sums). The plain forms (T = double,
-// or float) sum plainly in the order of the slices.
+// KS: sums in FP64 (the FP32 form with one or two bands per launch; three or
+// four bands sum in FP32: their sums would not fit in registers otherwise). A
+// product and sum is a conversion and one FP64 instruction per value, where a
+// compensated FP32 sum in as many registers takes four (one band of 24 slices
+// of 64^3 24.3 -> 23.1 us, two of 21 slices of 96^3 65 -> 61.5), and the
+// sum's error is that of its inputs. The plain forms (T = double, or float) sum
+// in T in the order of the slices.
 template <typename T, int L, int NB_, typename S, int PF, int IN, bool KS>
 __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(FusedDev<T> a, ColSet s0, ColSet s1,
                                                                            const cx<T> *__restrict__ tw_g) {
@@ -116,8 +161,7 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
     constexpr int RSTEP = NT / CPW;                        // = threads per column
     constexpr int GROWS = (HP + RSTEP - 1) / RSTEP;        // octant rows loaded per thread
     constexpr int NO = PAR ? 2 : 1;                        // output columns per input column
-    constexpr bool CS = KS;
-    constexpr int CB = sizeof(cx<T>);                      // bytes of a complex value
+        constexpr int CB = sizeof(cx<T>);                      // bytes of a complex value
     // FP64 lines are twice as wide: one line buffer (a barrier more per
     // exchange) leaves room for a second workgroup on the CU
     constexpr bool DB = sizeof(T) == 4;
@@ -157,8 +201,6 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
     const int c = threadIdx.x % CPW, t = threadIdx.x / CPW;
     const int H = L / 2;
     const int w = blockIdx.x;
-    int64_t pos = (int64_t)w * a.W / a.P;
-    const int64_t end = (int64_t)(w + 1) * a.W / a.P;
 
     auto segment = [&](const int64_t tile, const int k0, const int k1) {
 
@@ -193,16 +235,14 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
             if constexpr (PAR) gdel = fold(q + H, L) - fold(q, L);
         }
 
-        cx<T> sum[NO][NB_][E], cmp[NO][CS ? NB_ : 1][CS ? E : 1];
+        using A = std::conditional_t<KS, double, T>;
+        cx<A> sum[NO][NB_][E];
 #pragma unroll
         for (int o = 0; o < NO; ++o)
 #pragma unroll
             for (int b = 0; b < NB_; ++b)
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    sum[o][b][e] = mk((T)0, (T)0);
-                    if constexpr (CS) cmp[o][b][e] = mk((T)0, (T)0);
-                }
+                for (int e = 0; e < E; ++e) sum[o][b][e] = mk((A)0, (A)0);
 
         // Byte offsets, off workgroup-uniform bases (a slice spectrum is below
         // 4 GiB): of this thread's first input element, the others being whole
@@ -238,7 +278,7 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
 
         // The slice loop runs to a multiple of PF with no branch in its body:
         // slices past k1 read slice k1-1 again (valid, recently read memory)
-        // with kernel weight 0, which leaves the compensated sum's value
+        // with kernel weight 0, which leaves the sum's value
         // unchanged. Branch-free, every wait for a load counts exactly the
         // loads issued after it, so the prefetched slices stay in flight.
         const int kend = k0 + (k1 - k0 + PF - 1) / PF * PF;
@@ -311,23 +351,14 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
                         if (rf < HP) glk[(b * NO + o) * HP * CPW + rf * CPW + c] = gw[b] * gn[b][o][jj];
                     }
         };
-        // compensated (Kahan) sum over slices of output o, or the plain sum
+        // sum over slices of output o
         auto mac = [&](int o, const T *glk, const cx<T>(&v)[E]) {
 #pragma unroll
             for (int b = 0; b < NB_; ++b)
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     const T gv = glk[(b * NO + o) * HP * CPW + gslot[e]];
-                    if constexpr (CS) {
-                        const T yx = gv * v[e].x - cmp[o][b][e].x, yy = gv * v[e].y - cmp[o][b][e].y;
-                        const T tx = sum[o][b][e].x + yx, ty = sum[o][b][e].y + yy;
-                        cmp[o][b][e].x = (tx - sum[o][b][e].x) - yx;
-                        cmp[o][b][e].y = (ty - sum[o][b][e].y) - yy;
-                        sum[o][b][e].x = tx;
-                        sum[o][b][e].y = ty;
-                    } else {
-                        sum[o][b][e] = mk(fma_(gv, v[e].x, sum[o][b][e].x), fma_(gv, v[e].y, sum[o][b][e].y));
-                    }
+                    sum[o][b][e] = mk(fma_((A)gv, (A)v[e].x, sum[o][b][e].x), fma_((A)gv, (A)v[e].y, sum[o][b][e].y));
                 }
         };
         load_g(k0);
@@ -458,11 +489,7 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
             for (int o = 0; o < NO; ++o) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    if constexpr (CS) {
-                        y[o][e] = sum[o][b][e] - cmp[o][b][e];
-                    } else {
-                        y[o][e] = sum[o][b][e];
-                    }
+                    y[o][e] = mk((T)sum[o][b][e].x, (T)sum[o][b][e].y);
                     if (o == 0 && has_dc && EF::out_pos(t, e) == 0) y[o][e] = mk((T)0, (T)0);
                 }
                 // the last forward pass's placement is the first inverse pass's
@@ -488,39 +515,353 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
             for (int o = 0; o < NO; ++o) put(b, o, y[o]);
         }
         };
-    if (a.rounds) {
-        // whole tiles in rounds: all workgroups sweep the slices together
-        // main tiles per row (0: rows do not split into whole tiles, identity order)
-        const int npb = (L / 2) % CPW == 0 ? (int)((L / 2) / CPW) : 0;
-        constexpr int GP = fused_gp(CPW, sizeof(T));
-        const int nrow = PAR ? L / 2 : L;
-        const int64_t full = a.tiles / a.P * a.P;   // slots of the whole rounds
-        for (int64_t slot = w; slot < full; slot += a.P)
-            segment(fused_slot_tile(slot, s0.n_wgs, nrow, npb, GP), 0, a.kmax);
-        // the tiles of the remaining slots (fewer than P) would leave most
-        // workgroups idle for a whole round: their (tile, slice) pairs are
-        // split evenly over all workgroups instead. Only a workgroup's first
-        // segment can start inside a tile; it goes to the workgroup's part
-        // slot, and fused_rest_merge_kernel adds the parts of each tile.
-        const int64_t U = (a.tiles - full) * a.kmax;
-        int64_t u = (int64_t)w * U / a.P;
-        const int64_t ue = (int64_t)(w + 1) * U / a.P;
-        while (u < ue) {
-            const int64_t i = u / a.kmax;
-            const int k0 = (int)(u % a.kmax);
-            const int k1 = (int)std::min<int64_t>(a.kmax, k0 + (ue - u));
-            u += k1 - k0;
-            segment(fused_slot_tile(full + i, s0.n_wgs, nrow, npb, GP), k0, k1);
-        }
+    fused_walk<L, CPW, PAR>(a, s0, w, segment);
+}
+
+// ---------------------------------------------------------------------------
+// The same pass with one of the z transform's two exchanges between lanes
+//
+// L = 8 RM 8 (128 and 256 = 8.2.8 and 8.4.8), eight elements per thread.
+// Thread t of a column holds the first pass's inputs t + (L/8) r. Its outputs
+// r1 = 0..7 sit at positions 8t + r1, and a middle butterfly combines the same
+// r1 of the threads t, t + 8, .. (RM of them). With wave w taking the threads
+// t = w + NW g (NW waves, g the lane's row of 16, one lane per column), those
+// threads are rows of one wave: the exchange is a transpose between registers
+// and rows of lanes (v_permlane32_swap, v_permlane16_swap: one instruction per
+// 32-bit value and step instead of an LDS write, a barrier and a read). Only
+// the exchange before the last pass goes through LDS, so a slice has one
+// barrier, and its line buffers alternate by slice. Loads, stores and LDS
+// accesses stay whole 128-byte rows.
+//
+// Kernel values are read straight to the registers that use them (both folds
+// of a row, off one offset each), without LDS staging; the transform's
+// twiddles stay in registers across slices; the next slice's inputs are in
+// flight during the whole of the current one.
+//
+// With the spectra in cache (the instantaneous field) 256^3 x 40 takes 490 us
+// of this pass against 570 for fused_z_kernel, so the instructions no longer
+// bound it; streaming them from HBM it takes 741 us against 795 (4.1 TB/s: rows
+// of 128 bytes 256 KiB apart; a kernel that only reads them takes 540).
+// Two bands: 826 us for 20 slices against 1550, one set of line buffers and no
+// spilled prefetch. 128^3 x 24: 49 us against 53 (compute bound, three
+// workgroups per CU in both). 512 = 8.8.8 was slower this way (four bands of 12
+// slices 4.85 ms against 4.63): its transposes need lanes 8 apart, three
+// instructions a value, and four bands' kernel values two loads each.
+// ---------------------------------------------------------------------------
+template <int L> struct LaneShape {
+    static constexpr int RM = L / 64;                       // middle radix
+    static constexpr int CPW = 16;                          // columns per workgroup
+    static constexpr int TPL = L / 8, NT = CPW * TPL, NW = NT / 64, Q = 8 / RM;
+    static_assert(RM == 2 || RM == 4, "L = 128 or 256");
+    static_assert(TPL == NW * 4, "a wave holds four threads of each column");
+};
+
+// a of the upper half of the lanes (or of the odd rows of 16) and b of the
+// lower half (the even rows) change places
+template <int LANES> __device__ __forceinline__ void lane_swap(float &a, float &b) {
+    const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+    static_assert(LANES == 16 || LANES == 32, "");
+    const auto r = LANES == 32 ? __builtin_amdgcn_permlane32_swap(ua, ub, false, false)
+                               : __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+template <int LANES> __device__ __forceinline__ void lane_swap(cx<float> &a, cx<float> &b) {
+    lane_swap<LANES>(a.x, b.x);
+    lane_swap<LANES>(a.y, b.y);
+}
+
+// A 32-bit offset kept as such: extended where it is added to its uniform base
+// it goes into the load instruction; extended ahead of a loop, every load
+// forms a 64-bit address of its own (32 instructions and as many registers
+// per slice).
+__device__ __forceinline__ void keep32(uint32_t &v) { asm volatile("" : "+v"(v)); }
+
+template <bool NT> __device__ __forceinline__ cx<float> ld_spec(const char *p) {
+    if constexpr (NT) {
+        typedef float f2v __attribute__((ext_vector_type(2)));
+        const f2v v = __builtin_nontemporal_load((const f2v *)p);
+        return mk(v[0], v[1]);
     } else {
-        while (pos < end) {
-            const int64_t tile = pos / a.kmax;
-            const int k0 = (int)(pos % a.kmax);
-            const int k1 = (int)std::min<int64_t>(a.kmax, k0 + (end - pos));
-            pos += k1 - k0;
-            segment(tile, k0, k1);
+        return *(const cx<float> *)p;
+    }
+}
+
+template <int L> struct LaneTw {
+    cx<float> mid[8], last[8];   // forward twiddles: middle pass (q, r at q RM + r), last pass (r)
+};
+
+template <int L, bool FWD> struct LaneEngine {
+    using SH = LaneShape<L>;
+    static constexpr int RM = SH::RM, Q = SH::Q, TPL = SH::TPL;
+    __device__ __forceinline__ static cx<float> wmul(cx<float> v, cx<float> w) {
+        return FWD ? cmul(v, w) : cmul(v, conj(w));
+    }
+    // Middle butterfly q of the thread is r1(q) = element of its first pass's outputs
+    __device__ __forceinline__ static int r1(int g, int q) {
+        return RM == 2 ? 4 * (g >> 1) + q : 4 * q + g;
+    }
+    // position of output 0 of middle butterfly q (output r: 8 r further)
+    __device__ __forceinline__ static int mid_pos(int w, int g, int q) {
+        const int t0 = RM == 2 ? w + SH::NW * (g & 1) : w;
+        return t0 * 8 * RM + r1(g, q);
+    }
+    // passes 1 and 2 of the line in x, stored to the line buffer
+    __device__ __forceinline__ static void first(cx<float> (&x)[8], cx<float> *lds, int w, int g, int c,
+                                                 const LaneTw<L> &tw) {
+        dft8<FWD>(x);
+        cx<float> v[Q][RM];
+        if constexpr (RM == 2) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                lane_swap<32>(x[q], x[q + 4]);
+                v[q][0] = x[q];
+                v[q][1] = x[q + 4];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                cx<float> *a = x + 4 * q;
+                lane_swap<32>(a[0], a[2]);
+                lane_swap<32>(a[1], a[3]);
+                lane_swap<16>(a[0], a[1]);
+                lane_swap<16>(a[2], a[3]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[q][r] = a[r];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+#pragma unroll
+            for (int r = 1; r < RM; ++r) v[q][r] = wmul(v[q][r], tw.mid[q * RM + r]);
+            dft<RM, FWD>(v[q]);
+            const int p0 = mid_pos(w, g, q);
+#pragma unroll
+            for (int r = 0; r < RM; ++r) lds[(p0 + 8 * r) * SH::CPW + c] = v[q][r];
         }
     }
+    // last pass: element e is the output at position t + TPL e
+    __device__ __forceinline__ static void rest(cx<float> (&y)[8], const cx<float> *lds, int t, int c,
+                                                const LaneTw<L> &tw) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) y[r] = lds[(t + TPL * r) * SH::CPW + c];
+#pragma unroll
+        for (int r = 1; r < 8; ++r) y[r] = wmul(y[r], tw.last[r]);
+        dft8<FWD>(y);
+    }
+};
+
+// NT: the spectra are read with non-temporal loads.
+template <int L, int NB_, int IN, bool NT_>
+__global__ __launch_bounds__((LaneShape<L>::NT)) void fused_lane_kernel(FusedDev<float> a, ColSet s0, ColSet s1,
+                                                                        const cx<float> *__restrict__ tw_g) {
+    static_assert(IN == 0 || IN == 1, "y-transformed slices, plain or in the parity layout");
+    constexpr bool PAR = IN == 1;
+    using SH = LaneShape<L>;
+    using EF = LaneEngine<L, true>;
+    using EI = LaneEngine<L, false>;
+    constexpr int CPW = SH::CPW, TPL = SH::TPL, NO = PAR ? 2 : 1, HP = L / 2 + 1, H = L / 2;
+    using A = double;   // sums in FP64, as in fused_z_kernel
+    __shared__ cx<float> buf[2][NO][L * CPW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane % CPW, g = lane / CPW;
+    const int t = w + SH::NW * g;
+    const int wg = blockIdx.x;
+    LaneTw<L> tw;
+#pragma unroll
+    for (int q = 0; q < SH::Q; ++q)
+#pragma unroll
+        for (int r = 0; r < SH::RM; ++r) tw.mid[q * SH::RM + r] = tw_g[EF::r1(g, q) * (L / (8 * SH::RM)) * r];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) tw.last[r] = tw_g[t * r];
+    // the FP64 band means (DC mode), once per launch, by the first wave of
+    // workgroup 0: mu_b = inv_n3 sum_k G^_{k,b}(0) S^_k(0)
+    if (a.mu && wg == 0 && threadIdx.x < 64) {
+#pragma unroll
+        for (int b = 0; b < NB_; ++b) {
+            if (b >= a.nb) break;
+            double v = 0.0;
+            for (int k = threadIdx.x; k < a.K; k += 64) {
+                const int slot = a.frozen >= 0 ? a.frozen : (k + a.ring < a.K ? k + a.ring : k + a.ring - a.K);
+                v += a.g0[(int64_t)k * a.B + a.band0 + b] * a.sk[slot];
+            }
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+            if (threadIdx.x == 0) a.mu[a.band0 + b] = v * a.inv_n3;
+        }
+    }
+
+    auto segment = [&](const int64_t tile, const int k0, const int k1) {
+        lds_barrier();   // readers of the line buffers in the previous segment are done
+        const bool is_main = tile < s0.n_wgs;
+        const ColSet &s = is_main ? s0 : s1;
+        const int64_t col0 = (is_main ? tile : tile - s0.n_wgs) * CPW;
+        const int64_t col = col0 + c;
+        const bool col_ok = col < s.n_cols;
+        // columns past the end compute on a valid column and are not stored
+        const int64_t ccol = col_ok ? col : col0;
+        const int64_t cbase = col_base(s, ccol);
+        // row (y frequency) of the column; in the parity layout the second
+        // output and the O input are obase elements further
+        const int q = is_main ? (int)(ccol / H) : (int)ccol;
+        const int64_t obase = is_main ? (int64_t)H * H : (int64_t)H;
+        const cx<float> wq = PAR ? tw_g[q] : mk(1.f, 0.f);   // W_N^q
+        int gbase, grow, gdel = 0;
+        if (is_main) {
+            const int cc = (int)ccol;
+            gbase = fold(q, L) * H + cc % H;
+            grow = HP * H;
+            if constexpr (PAR) gdel = (fold(q + H, L) - fold(q, L)) * H;
+        } else {
+            gbase = HP * HP * H + fold(q, L);
+            grow = HP;
+            if constexpr (PAR) gdel = fold(q + H, L) - fold(q, L);
+        }
+        cx<A> sum[NO][NB_][8];
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int b = 0; b < NB_; ++b)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum[o][b][e] = mk((A)0, (A)0);
+
+        // byte offsets off workgroup-uniform bases: element e is e row steps
+        // further; the kernel rows fold(t + TPL e) are t + TPL e for e < 4 and
+        // H - t - TPL (e - 4) from there
+        const uint32_t xoff = (uint32_t)((cbase + (int64_t)t * s.row_stride) * 8);
+        const int64_t rsb = s.row_stride * 8 * TPL;
+        const uint32_t glo = (uint32_t)((gbase + t * grow) * 4), ghi = (uint32_t)((gbase + (H - t) * grow) * 4);
+        const int64_t grb = (int64_t)grow * 4 * TPL;
+        const int64_t obytes = obase * 8;
+        auto spec_at = [&](int k) {
+            int slot = (k < k1 ? k : k1 - 1) + a.ring;
+            if (slot >= a.K) slot -= a.K;
+            if (a.frozen >= 0) slot = a.frozen;
+            return (const char *)(a.spec + (int64_t)slot * a.spec_stride);
+        };
+        // inputs of the next slice, in flight during the whole of the current
+        // one (slices past the end read the last again)
+        cx<float> xn[NO][8];
+        auto fill = [&](int k) {
+            const char *src = spec_at(k);
+            uint32_t off = xoff;
+            keep32(off);
+#pragma unroll
+            for (int o = 0; o < NO; ++o)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xn[o][e] = ld_spec<NT_>(src + o * obytes + e * rsb + off);
+        };
+        float gv[NB_][NO][8], gw[NB_];
+        auto load_g = [&](int k) {
+#pragma unroll
+            for (int b = 0; b < NB_; ++b) {
+                // a band without a kernel for slice k reads a valid octant with
+                // weight 0 (one band per launch: always on); a band past nb
+                // reads the first handled band's
+                const bool on = NB_ == 1 || k < a.Kc[b];
+                gw[b] = on ? 1.f : 0.f;
+                const int kb = on ? k : 0, bb = b < a.nb ? b : 0;
+                const char *gp = (const char *)(a.ghat + ((int64_t)kb * a.B + a.band0 + bb) * a.oct_stride);
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    // gdel < 0 for q > N/4: formed in 32 bits, where it wraps to
+                    // the true (nonnegative) offset
+                    const uint32_t od = (uint32_t)(o * gdel) * 4u;
+                    uint32_t lo = glo + od, hi = ghi + od;
+                    keep32(lo);
+                    keep32(hi);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        gv[b][o][e] = *(const float *)(gp + (e < 4 ? e * grb : -(e - 4) * grb) + (e < 4 ? lo : hi));
+                }
+            }
+        };
+        auto mac = [&](int o, const cx<float>(&v)[8]) {
+#pragma unroll
+            for (int b = 0; b < NB_; ++b)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float gg = NB_ == 1 ? gv[b][o][e] : gw[b] * gv[b][o][e];
+                    sum[o][b][e] = mk(fma_((A)gg, (A)v[e].x, sum[o][b][e].x), fma_((A)gg, (A)v[e].y, sum[o][b][e].y));
+                }
+        };
+        fill(k0);
+        for (int k = k0; k < k1; ++k) {
+            cx<float>(*lb)[L * CPW] = buf[(k - k0) & 1];
+            load_g(k);
+            cx<float> x[NO][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const cx<float> u = xn[0][e];
+                if constexpr (PAR) {
+                    // last radix-2 step of the y transform: E +- W_N^q O
+                    const cx<float> y = xn[1][e];
+                    const float ux = fma_(wq.x, y.x, -wq.y * y.y), uy = fma_(wq.x, y.y, wq.y * y.x);
+                    x[0][e] = mk(u.x + ux, u.y + uy);
+                    x[1][e] = mk(u.x - ux, u.y - uy);
+                } else {
+                    x[0][e] = u;
+                }
+            }
+            fill(k + 1);
+            // a line buffer written here was last read two slices ago, before
+            // the barrier that every thread has passed since
+#pragma unroll
+            for (int o = 0; o < NO; ++o) EF::first(x[o], lb[o], w, g, c, tw);
+            lds_barrier();
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                cx<float> y[8];
+                EF::rest(y, lb[o], t, c, tw);
+                mac(o, y);
+            }
+        }
+
+        // the (0,0,0) bin: row 0 of main column 0
+        const bool has_dc = a.zero_dc && is_main && col == 0;
+        const bool primary = k0 == 0;
+#pragma unroll
+        for (int b = 0; b < NB_; ++b) {
+            if (b >= a.nb) break;   // (uniform: the barriers below stay matched)
+            // the other buffer: its last readers are past a barrier
+            cx<float>(*lb)[L * CPW] = buf[(k1 - k0 + b) & 1];
+            cx<float> y[NO][8];
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[o][e] = mk((float)sum[o][b][e].x, (float)sum[o][b][e].y);
+                if (o == 0 && has_dc && t == 0) y[o][0] = mk(0.f, 0.f);
+                EI::first(y[o], lb[o], w, g, c, tw);
+            }
+            lds_barrier();
+#pragma unroll
+            for (int o = 0; o < NO; ++o) EI::rest(y[o], lb[o], t, c, tw);
+            if constexpr (PAR) {
+                // first radix-2 step of the inverse y transform, split by the
+                // parity of the output rows (see fused_z_kernel)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const cx<float> u = y[0][e], v = y[1][e];
+                    const cx<float> d = mk(u.x - v.x, u.y - v.y);
+                    y[0][e] = mk(u.x + v.x, u.y + v.y);
+                    y[1][e] = mk(fma_(wq.x, d.x, wq.y * d.y), fma_(wq.x, d.y, -wq.y * d.x));   // conj(W^q) d
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                if (primary) {
+                    cx<float> *dst = a.acc + (int64_t)b * a.acc_stride + o * obase;
+                    if (col_ok)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            dst[(uint32_t)(cbase + (int64_t)(t + TPL * e) * s.row_stride)] = y[o][e];
+                } else {
+                    cx<float> *dst = a.part + (int64_t)b * a.part_stride + (int64_t)(NO * wg + o) * (L * CPW) + c;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) dst[(t + TPL * e) * CPW] = y[o][e];
+                }
+            }
+        }
+    };
+    fused_walk<L, CPW, PAR>(a, s0, wg, segment);
 }
 
 // Parts of the tiles split by slices after the whole rounds (the rounds
@@ -549,7 +890,7 @@ void launch_fused_split(int *tab, int64_t tiles, int64_t kmax, int64_t P, int64_
 
 // Schedule that fixes the tiling of the fused pass for N: the 16-element
 // schedule, except at N = 384 and 512, where only the 8-element one keeps
-// its per-band compensated sums and prefetch ring in registers.
+// its per-band sums and prefetch ring in registers.
 template <int N> constexpr bool fused_sched8_only() { return N == 384 || N == 512; }
 template <int N> using FusedTiling = std::conditional_t<fused_sched8_only<N>(), Sched8<N>, Sched<N>>;
 
@@ -579,17 +920,14 @@ static void fused_sets(ColSet &s0, ColSet &s1, bool pair = false) {
     s1.n_wgs = (int32_t)((s1.n_cols + CPW - 1) / CPW);
 }
 
-template <int N, int NB, typename S, int PF, int IN>
-static int fused_slots() {
+// Workgroups of one kernel that the device holds at a time.
+template <auto KERNEL, int NT> static int fused_slots() {
     static int cached = 0;
     if (cached) return cached;
     int dev = 0, per_cu = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_z_kernel<float, N, NB, S, PF, IN, (NB <= 2)>, FusedShape<float, N, S>::NT,
-                                                     0) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, NT, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     cached = per_cu * prop.multiProcessorCount;
     return cached;
 }
@@ -599,20 +937,13 @@ static int fused_slots() {
 // them once for four bands instead of twice pays most.
 template <int N, int PF, int IN> constexpr bool fused_nb4() { return (N == 384 || N == 512) && PF == 1 && IN != 1; }
 
-template <int N, typename S, int PF, int IN>
-static hipError_t fused_launch(const FusedArgs &fa, const void *tw, hipStream_t st, ColSet s0, ColSet s1,
-                               int64_t tiles, int kmax) {
-    static_assert(FusedShape<float, N, S>::CPW == FusedShape<float, N, FusedTiling<N>>::CPW, "variants share the tiling");
-    constexpr bool PAR = IN == 1;
-    int slots = 0;
-    if (fa.nband > 2) {
-        if constexpr (fused_nb4<N, PF, IN>()) slots = fused_slots<N, 4, S, PF, IN>();
-        else return hipErrorInvalidValue;
-    } else {
-        slots = fa.nband == 2 ? fused_slots<N, 2, S, PF, IN>() : fused_slots<N, 1, S, PF, IN>();
-    }
+// Launch of kernel KERNEL (one of the instances below) over the tiles.
+template <int N, int CPW, int NT, bool PAR, auto KERNEL>
+static hipError_t fused_go(const FusedArgs &fa, const void *tw, hipStream_t st, ColSet s0, ColSet s1, int64_t tiles,
+                           int kmax) {
+    static_assert(CPW == FusedShape<float, N, FusedTiling<N>>::CPW, "variants share the tiling");
     // (two part slots per workgroup with two outputs per tile)
-    const int64_t P = std::min<int64_t>(std::min<int64_t>(slots, tiles), fa.max_parts / (PAR ? 2 : 1));
+    const int64_t P = std::min<int64_t>(std::min<int64_t>(fused_slots<KERNEL, NT>(), tiles), fa.max_parts / (PAR ? 2 : 1));
     FusedDev<float> d;
     d.spec = (const cx<float> *)fa.spec; d.spec_stride = fa.spec_stride;
     d.ghat = (const float *)fa.ghat; d.oct_stride = fa.oct_stride;
@@ -628,21 +959,10 @@ static hipError_t fused_launch(const FusedArgs &fa, const void *tw, hipStream_t 
     // the rounds mode splits no tile and its inverse pass does not read it
     if (!fa.rounds)
         launch_fused_split((int *)fa.split_tab, tiles, kmax, P, d.W, PAR ? 1 : 0, s0.n_wgs, tiles, st);
-    constexpr int NT = FusedShape<float, N, S>::NT;
-    if (fa.nband > 2) {
-        if constexpr (fused_nb4<N, PF, IN>())
-            hipLaunchKernelGGL((fused_z_kernel<float, N, 4, S, PF, IN, false>), dim3((unsigned)P), dim3(NT), 0, st, d, s0, s1,
-                               (const cx<float> *)tw);
-    } else if (fa.nband == 2)
-        hipLaunchKernelGGL((fused_z_kernel<float, N, 2, S, PF, IN, true>), dim3((unsigned)P), dim3(NT), 0, st, d, s0, s1,
-                           (const cx<float> *)tw);
-    else
-        hipLaunchKernelGGL((fused_z_kernel<float, N, 1, S, PF, IN, true>), dim3((unsigned)P), dim3(NT), 0, st, d, s0, s1,
-                           (const cx<float> *)tw);
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)P), dim3(NT), 0, st, d, s0, s1, (const cx<float> *)tw);
     const int64_t full = tiles / P * P;
     if (fa.rounds && full < tiles) {
         // parts of the tiles split by slices after the whole rounds
-        constexpr int CPW = FusedShape<float, N, S>::CPW;
         RestMerge m;
         m.acc = (cx<float> *)fa.acc; m.acc_stride = fa.acc_stride;
         m.part = (const cx<float> *)fa.part; m.part_stride = fa.part_stride;
@@ -654,6 +974,44 @@ static hipError_t fused_launch(const FusedArgs &fa, const void *tw, hipStream_t 
         launch_fused_rest_merge(m, s0, s1, st);
     }
     return hipGetLastError();
+}
+
+template <int N, typename S, int PF, int IN>
+static hipError_t fused_launch(const FusedArgs &fa, const void *tw, hipStream_t st, ColSet s0, ColSet s1,
+                               int64_t tiles, int kmax) {
+    using SH = FusedShape<float, N, S>;
+#define GO_(NB) return fused_go<N, SH::CPW, SH::NT, IN == 1, fused_z_kernel<float, N, NB, S, PF, IN, (NB <= 2)>>(fa, tw, st, s0, s1, tiles, kmax)
+    if (fa.nband > 2) {
+        if constexpr (fused_nb4<N, PF, IN>()) GO_(4);
+        else return hipErrorInvalidValue;
+    }
+    if (fa.nband == 2) GO_(2);
+    GO_(1);
+#undef GO_
+}
+
+// Grid sides with the lane-exchange kernel, the last variant there.
+template <int N> constexpr bool fused_lane() { return N == 128 || N == 256; }
+constexpr int kLaneVariant = 4;
+
+template <int N, int IN>
+static hipError_t fused_lane_launch(const FusedArgs &fa, const void *tw, hipStream_t st, ColSet s0, ColSet s1,
+                                    int64_t tiles, int kmax) {
+    using SH = LaneShape<N>;
+    // Spectra that the last-level cache (256 MB) cannot hold stream past it: at
+    // 256^3 x 40 (2.7 GB) 741 us with non-temporal loads against 784; slices
+    // that do fit are found there (128^3 x 24, 200 MB: 57 us against 49).
+    const bool nt = (fa.frozen >= 0 ? 1 : kmax) * fa.spec_stride * 8 > ((int64_t)256 << 20);
+#define GO_(NB, NT_)                                                                                               \
+    return fused_go<N, SH::CPW, SH::NT, IN == 1, fused_lane_kernel<N, NB, IN, NT_>>(fa, tw, st, s0, s1, tiles, kmax)
+    if (fa.nband == 2) {
+        if (nt) GO_(2, true);
+        GO_(2, false);
+    }
+    if (fa.nband != 1) return hipErrorInvalidValue;
+    if (nt) GO_(1, true);
+    GO_(1, false);
+#undef GO_
 }
 
 // parity-layout input: compiled where a half-plane xy shape exists (the
@@ -668,7 +1026,13 @@ static hipError_t fused_sched(const FusedArgs &fa, const void *tw, hipStream_t s
     // variant = 2 * schedule + (prefetch depth 1 ? 1 : 0); schedule 1 = Sched8
     // (N = 384, 512 compile only the Sched8 pair)
     // (three or four bands per launch: prefetch depth 1 only)
-    const int sched = fused_sched8_only<N>() ? 1 : fa.variant / 2, pf = fa.variant % 2 || fa.nband > 2 ? 1 : 2;
+    if constexpr (fused_lane<N>() && IN != 2) {
+        if (fa.variant == kLaneVariant) return fused_lane_launch<N, IN>(fa, tw, st, s0, s1, tiles, kmax);
+    }
+    // (slices transformed along z already: the lane variant stands for the
+    // eight-element schedule with two slices prefetched, the fastest there)
+    const int var = fused_lane<N>() && fa.variant == kLaneVariant ? 2 : fa.variant;
+    const int sched = fused_sched8_only<N>() ? 1 : var / 2, pf = var % 2 || fa.nband > 2 ? 1 : 2;
     if constexpr (HasSched8<N>::value) {
         if (sched == 1)
             return pf == 1 ? fused_launch<N, Sched8<N>, 1, IN>(fa, tw, st, s0, s1, tiles, kmax)

@@ -126,7 +126,7 @@ hipError_t launch_col_z_tiled(int n, const void *in, void *out, const void *tw_f
 
 // Fused z pass for FP32: for each column of the y-transformed slices,
 // forward z transform of every slice k < kcount[b], multiply by G^_{k,b},
-// sum over k (compensated with one or two bands per launch, plain with
+// sum over k (in FP64 with one or two bands per launch, in FP32 with
 // three or four), inverse z transform, store to acc[b].
 struct FusedArgs {
     const void *spec;        // K slices, stride spec_elems(n)
