@@ -148,10 +148,10 @@ __global__ __launch_bounds__((RowShape<T, N / 2>::NT)) void x_inv_kernel(
 // column passes (y or z), in place; grid = main WGs then nyq WGs.
 // Lanes walk the columns (col_stride 1) or, for row-contiguous sets, the
 // rows of a column, so that global accesses stay coalesced either way.
-// With COMBINE (inverse y pass of a fused FP32 accumulator) the second part
+// With COMBINE (1: the tiles in tab, 2: every tile; inverse y pass of a fused FP32 accumulator) the second part
 // of a tile that the persistent fused pass split between two workgroups is
 // added while loading: element (z, y=q, p) belongs to fused tile
-// (q*H + p) / cpw_z (main) or tiles_main + q / cpw_z (nyq), at row z.
+// (q*H + p) / CZ (main) or TMAIN + q / CZ (nyq), CZ columns a tile, at row z.
 // ---------------------------------------------------------------------------
 template <int CPW, int TPL>
 __device__ __forceinline__ void col_lane(bool rowfast, int &c, int &t) {
@@ -164,11 +164,10 @@ __device__ __forceinline__ void col_lane(bool rowfast, int &c, int &t) {
 // columns (the last one narrower), a tile's rows contiguous:
 //   element (row r, column col) at set_off + c0 L + r w + (col - c0),
 //   c0 = col - col mod tcpw, w = min(tcpw, n_cols - c0).
-template <typename T, int L, bool FWD, bool COMBINE, bool TILED = false>
+template <typename T, int L, bool FWD, int COMBINE, bool TILED = false>
 __global__ __launch_bounds__((ColShape<T, L>::NT)) void col_kernel(
     cx<T> *data0, int64_t data_stride, ColSet s0, ColSet s1, const cx<T> *__restrict__ tw_g,
-    const int *__restrict__ tab, const cx<T> *__restrict__ part, int64_t tiles_main, int cpw_z,
-    cx<T> *__restrict__ out = nullptr, int tcpw = 1) {
+    const int *__restrict__ tab, const cx<T> *__restrict__ part, cx<T> *__restrict__ out = nullptr, int tcpw = 1) {
     // workgroup blockIdx.x handles tile (blockIdx.x % per) of spectrum (blockIdx.x / per)
     const int per = s0.n_wgs + s1.n_wgs;
     const int bid = blockIdx.x % per;
@@ -192,20 +191,20 @@ __global__ __launch_bounds__((ColShape<T, L>::NT)) void col_kernel(
     for (int e = 0; e < E; ++e) {
         const int j = EN::in_pos(t, e);
         x[e] = ok ? data[base + j * s.row_stride] : mk((T)0, (T)0);
-        if constexpr (COMBINE) {
+        if constexpr (COMBINE != 0) {
             if (ok) {
+                constexpr int CZ = fused_cols<L>(), H = L / 2, TMAIN = (L * H + CZ - 1) / CZ;
                 int zt, zc, z;
                 if (first) {
-                    const int H = L / 2;
                     z = (int)(col / H);
                     const int q = j * H + (int)(col % H);
-                    zt = q / cpw_z; zc = q % cpw_z;
+                    zt = q / CZ; zc = q % CZ;
                 } else {
                     z = (int)col;
-                    zt = (int)(tiles_main + j / cpw_z); zc = j % cpw_z;
+                    zt = TMAIN + j / CZ; zc = j % CZ;
                 }
-                const int w = tab[zt];
-                if (w >= 0) x[e] = x[e] + part[((int64_t)w * L + z) * cpw_z + zc];
+                const int w = COMBINE == 2 ? zt : tab[zt];
+                if (COMBINE == 2 || w >= 0) x[e] = x[e] + part[((int64_t)w * L + z) * CZ + zc];
             }
         }
     }
@@ -361,11 +360,11 @@ static hipError_t col_t(int axis, bool fwd, void *spec, int64_t stride, int coun
     col_sets<T, N>(axis, s0, s1);
     const dim3 grid((unsigned)((s0.n_wgs + s1.n_wgs) * count));
     if (fwd)
-        hipLaunchKernelGGL((col_kernel<T, N, true, false>), grid, dim3(SH::NT), 0, st, (cx<T> *)spec, stride,
-                           s0, s1, (const cx<T> *)tw, nullptr, nullptr, (int64_t)0, 1);
+        hipLaunchKernelGGL((col_kernel<T, N, true, 0>), grid, dim3(SH::NT), 0, st, (cx<T> *)spec, stride,
+                           s0, s1, (const cx<T> *)tw, nullptr, nullptr);
     else
-        hipLaunchKernelGGL((col_kernel<T, N, false, false>), grid, dim3(SH::NT), 0, st, (cx<T> *)spec, stride,
-                           s0, s1, (const cx<T> *)tw, nullptr, nullptr, (int64_t)0, 1);
+        hipLaunchKernelGGL((col_kernel<T, N, false, 0>), grid, dim3(SH::NT), 0, st, (cx<T> *)spec, stride,
+                           s0, s1, (const cx<T> *)tw, nullptr, nullptr);
     return hipGetLastError();
 }
 
@@ -375,8 +374,8 @@ static hipError_t col_z_tiled_t(const void *in, void *out, const void *tw, hipSt
     using SH = ColShape<float, N>;
     ColSet s0, s1;
     col_sets<float, N>(2, s0, s1);
-    hipLaunchKernelGGL((col_kernel<float, N, true, false, true>), dim3(s0.n_wgs + s1.n_wgs), dim3(SH::NT), 0, st,
-                       (cx<float> *)in, (int64_t)0, s0, s1, (const cx<float> *)tw, nullptr, nullptr, (int64_t)0, 1,
+    hipLaunchKernelGGL((col_kernel<float, N, true, 0, true>), dim3(s0.n_wgs + s1.n_wgs), dim3(SH::NT), 0, st,
+                       (cx<float> *)in, (int64_t)0, s0, s1, (const cx<float> *)tw, nullptr, nullptr,
                        (cx<float> *)out, fused_cpw(N));
     return hipGetLastError();
 }
@@ -394,12 +393,16 @@ static hipError_t col_comb_t(void *spec, const void *tw, const int *tab, const v
     using SH = ColShape<float, N>;
     ColSet s0, s1;
     col_sets<float, N>(1, s0, s1);
-    // the fused pass tiles its N*H main columns by fused_cpw(N) columns
-    const int cpw_z = fused_cpw(N);
-    const int64_t tiles_main = ((int64_t)N * (N / 2) + cpw_z - 1) / cpw_z;
-    hipLaunchKernelGGL((col_kernel<float, N, false, true>), dim3(s0.n_wgs + s1.n_wgs), dim3(SH::NT), 0, st,
-                       (cx<float> *)spec, (int64_t)0, s0, s1, (const cx<float> *)tw, tab,
-                       (const cx<float> *)part, tiles_main, cpw_z);
+#define CC_(C)                                                                                                     \
+    hipLaunchKernelGGL((col_kernel<float, N, false, C>), dim3(s0.n_wgs + s1.n_wgs), dim3(SH::NT), 0, st,              \
+                       (cx<float> *)spec, (int64_t)0, s0, s1, (const cx<float> *)tw, tab, (const cx<float> *)part)
+    if (tab) {
+        CC_(1);
+    } else {
+        if constexpr (N <= 96) CC_(2);
+        else return hipErrorInvalidValue;
+    }
+#undef CC_
     return hipGetLastError();
 }
 

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace lc {
 
 // Workgroup barrier ordering LDS accesses only. __syncthreads() is a
@@ -580,6 +582,15 @@ template <typename T, int L, typename S> struct FusedShape {
     static constexpr int NT = CPW * TPL;
     static constexpr int PAD = 1;
 };
+
+// Schedule that fixes the tiling of the fused pass for N: the 16-element
+// schedule, except at N = 384 and 512, where only the 8-element one keeps
+// its per-band sums and prefetch ring in registers.
+template <int N> constexpr bool fused_sched8_only() { return N == 384 || N == 512; }
+template <int N> using FusedTiling = std::conditional_t<fused_sched8_only<N>(), Sched8<N>, Sched<N>>;
+
+// columns per tile of the FP32 form's fused pass
+template <int N> constexpr int fused_cols() { return FusedShape<float, N, FusedTiling<N>>::CPW; }
 
 // Launch shape of the row (x) passes for half-length L = N/2.
 template <typename T, int L> struct RowShape {

@@ -144,6 +144,7 @@ int fused_max_bands(int n) { return (n == 384 || n == 512) ? 4 : 2; }
 // eight-element schedule of depth 1, 68.5 us for 24 slices against 71.)
 int fused_default_variant(int n, int nband) {
     if (n == 256) return 4;
+    if (n == 96) return 1;    // (depth 1: both halves of every tile fit, see fused_go; 24 slices 68 -> 49 us)
     if (n == 128) return nband > 1 ? 3 : 4;
     if (n == 384) return 1;   // depth 1 is the instance without spills there
     const int s8 = fused_variants(n) > 2 ? 2 : 0;

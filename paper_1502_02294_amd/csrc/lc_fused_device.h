@@ -90,9 +90,17 @@ __device__ __forceinline__ int64_t fused_slot_tile(int64_t slot, int64_t main_ti
 }
 
 // The tiles and slices of workgroup w, as segment(tile, first slice, end).
+// rounds = 2 (few tiles): workgroup w takes a half of the slices of tile
+// w mod tiles, the first or the second.
 template <int L, int CPW, bool PAR, typename T, typename F>
 __device__ __forceinline__ void fused_walk(const FusedDev<T> &a, const ColSet &s0, int w, F &&segment) {
-    if (a.rounds) {
+    if (a.rounds == 2) {
+        const int npb = (L / 2) % CPW == 0 ? (int)((L / 2) / CPW) : 0;
+        const int half = w >= (int)a.tiles ? 1 : 0, mid = a.kmax / 2;
+        const int64_t tile = fused_slot_tile(half ? w - a.tiles : w, s0.n_wgs, PAR ? L / 2 : L, npb,
+                                             fused_gp(CPW, sizeof(T)));
+        segment(tile, half ? mid : 0, half ? a.kmax : mid);
+    } else if (a.rounds) {
         // whole tiles in rounds: all workgroups sweep the slices together
         // main tiles per row (0: rows do not split into whole tiles, identity order)
         const int npb = (L / 2) % CPW == 0 ? (int)((L / 2) / CPW) : 0;
@@ -476,7 +484,7 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
                     for (int e = 0; e < E; ++e)
                         dst[(uint32_t)(cbase + (int64_t)EI::out_pos(t, e) * s.row_stride)] = y[e];
             } else {
-                cx<T> *dst = a.part + (int64_t)b * a.part_stride + (int64_t)(NO * w + o) * (L * CPW) + c;
+                cx<T> *dst = a.part + (int64_t)b * a.part_stride + (NO * (a.rounds == 2 ? tile : (int64_t)w) + o) * (L * CPW) + c;
 #pragma unroll
                 for (int e = 0; e < E; ++e) dst[EI::out_pos(t, e) * CPW] = y[e];
             }
@@ -888,12 +896,6 @@ void launch_fused_rest_merge(const RestMerge &m, const ColSet &s0, const ColSet 
 void launch_fused_split(int *tab, int64_t tiles, int64_t kmax, int64_t P, int64_t W, int32_t pair, int64_t main_k,
                         int64_t count, hipStream_t st);
 
-// Schedule that fixes the tiling of the fused pass for N: the 16-element
-// schedule, except at N = 384 and 512, where only the 8-element one keeps
-// its per-band sums and prefetch ring in registers.
-template <int N> constexpr bool fused_sched8_only() { return N == 384 || N == 512; }
-template <int N> using FusedTiling = std::conditional_t<fused_sched8_only<N>(), Sched8<N>, Sched<N>>;
-
 // Schedule of the plain forms: eight elements per thread where it exists.
 template <int N> struct HasSched8 {
     static constexpr bool value = (N == 64 || N == 128 || N == 192 || N == 256 || N == 384 || N == 512);
@@ -937,13 +939,27 @@ template <auto KERNEL, int NT> static int fused_slots() {
 // them once for four bands instead of twice pays most.
 template <int N, int PF, int IN> constexpr bool fused_nb4() { return (N == 384 || N == 512) && PF == 1 && IN != 1; }
 
+// Whether a launch over `tiles` tiles splits each one's slices in two: both
+// halves of all tiles are resident together, a half is worth its prologue and
+// its inverse transform (four slices or more), and the parts have a slot per tile.
+inline bool fused_halves(int n, const FusedArgs &fa, int64_t tiles, int kmax, int64_t slots, bool par) {
+    return fa.halves && fa.rounds && !par && n <= 96 && 2 * tiles <= slots && kmax >= 8 && tiles <= fa.max_parts;
+}
+
 // Launch of kernel KERNEL (one of the instances below) over the tiles.
 template <int N, int CPW, int NT, bool PAR, auto KERNEL>
 static hipError_t fused_go(const FusedArgs &fa, const void *tw, hipStream_t st, ColSet s0, ColSet s1, int64_t tiles,
                            int kmax) {
     static_assert(CPW == FusedShape<float, N, FusedTiling<N>>::CPW, "variants share the tiling");
+    // Few tiles (N <= 96): a workgroup per tile walks all slices one after the
+    // other while most SIMDs have no wave; each tile's slices go to two
+    // workgroups, the second's sum to the part slot of the tile, which the
+    // inverse y pass adds. Field of one band, 24 slices: 24^3 63 -> 47 us, 48^3
+    // 47 -> 38, 96^3 66 -> 49; 64^3, 48 slices, 53 -> 40.
+    const int64_t slots = fused_slots<KERNEL, NT>();
+    const bool halves = fused_halves(N, fa, tiles, kmax, slots, PAR);
     // (two part slots per workgroup with two outputs per tile)
-    const int64_t P = std::min<int64_t>(std::min<int64_t>(fused_slots<KERNEL, NT>(), tiles), fa.max_parts / (PAR ? 2 : 1));
+    const int64_t P = halves ? 2 * tiles : std::min<int64_t>(std::min<int64_t>(slots, tiles), fa.max_parts / (PAR ? 2 : 1));
     FusedDev<float> d;
     d.spec = (const cx<float> *)fa.spec; d.spec_stride = fa.spec_stride;
     d.ghat = (const float *)fa.ghat; d.oct_stride = fa.oct_stride;
@@ -953,15 +969,16 @@ static hipError_t fused_go(const FusedArgs &fa, const void *tw, hipStream_t st, 
     d.part = (cx<float> *)fa.part; d.part_stride = fa.part_stride;
     d.zero_dc = fa.zero_dc;
     d.kmax = kmax; d.P = (int32_t)P; d.W = tiles * kmax;
-    d.rounds = fa.rounds; d.tiles = tiles;
+    d.rounds = halves ? 2 : fa.rounds; d.tiles = tiles;
     d.sk = fa.sk; d.g0 = fa.g0; d.inv_n3 = fa.inv_n3; d.mu = fa.mu; d.K = fa.K; d.ring = fa.ring; d.frozen = fa.frozen;
     // the split table serves the stream-K mode's merge in the inverse y pass;
     // the rounds mode splits no tile and its inverse pass does not read it
-    if (!fa.rounds)
+    if (!fa.rounds && !halves)
         launch_fused_split((int *)fa.split_tab, tiles, kmax, P, d.W, PAR ? 1 : 0, s0.n_wgs, tiles, st);
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)P), dim3(NT), 0, st, d, s0, s1, (const cx<float> *)tw);
     const int64_t full = tiles / P * P;
-    if (fa.rounds && full < tiles) {
+    if (fa.halves) *fa.halves = halves;
+    if (fa.rounds && !halves && full < tiles) {
         // parts of the tiles split by slices after the whole rounds
         RestMerge m;
         m.acc = (cx<float> *)fa.acc; m.acc_stride = fa.acc_stride;

@@ -480,16 +480,18 @@ template <typename F> int time_calls(hipStream_t st, int reps, F &&launch, doubl
 }
 
 // Inverse y pass of an FP32 accumulator after the fused z pass: the stream-K
-// mode's split tiles are merged while loading; the rounds mode splits none.
+// mode's split tiles, and the second halves of a launch that split every tile
+// (no table), are merged while loading; the rounds mode splits none otherwise.
 hipError_t inv_y_fused(int n, void *acc, const void *tw_full, const int *tab, const void *part, bool rounds,
-                       hipStream_t st) {
+                       bool halves, hipStream_t st) {
+    if (halves) return launch_col_y_inv_combine(n, acc, tw_full, nullptr, part, st);
     return rounds ? launch_col(n, false, 1, false, acc, tw_full, st)
                   : launch_col_y_inv_combine(n, acc, tw_full, tab, part, st);
 }
 
 // Inverse y + x pass of bands [b, b + nb) with the fused pass's schedule (the
 // stream-K mode's split tiles are merged while loading).
-InvArgs inv_args(const BoxPlan &bp, size_t cs, int b, int nb, bool parity) {
+InvArgs inv_args(const BoxPlan &bp, size_t cs, int b, int nb, bool parity, bool halves = false) {
     InvArgs a{};
     a.acc_stride = spec_elems(bp.n);
     a.acc = bp.acc + (size_t)b * a.acc_stride * cs;
@@ -498,8 +500,8 @@ InvArgs inv_args(const BoxPlan &bp, size_t cs, int b, int nb, bool parity) {
     a.tw_half = bp.tw_half; a.twist = bp.twist; a.tw_full = bp.tw_full;
     a.scale = 1.0 / ((double)bp.n * bp.n * bp.n);
     a.mu = bp.mu + b;
-    if (!bp.plain && !bp.fused_rounds) {
-        a.split_tab = bp.split_tab + (size_t)(b / bp.fused_bands) * bp.tiles;
+    if (!bp.plain && (halves || !bp.fused_rounds)) {
+        a.split_tab = halves ? nullptr : bp.split_tab + (size_t)(b / bp.fused_bands) * bp.tiles;
         a.part = bp.part;
         a.part_stride = bp.part_stride;
     }
@@ -641,15 +643,17 @@ int autotune_box_uncached(lc_plan_t *p, BoxPlan &bp) {
                 // with the layout's own inverse pass (fused inverse y + x for the
                 // parity layout; the inverse y pass otherwise, the x pass being
                 // the same in both)
+                bool halves = false;
+                fa.halves = &halves;
                 int rc = time_calls(p->stream, 2, [&]() {
                     hipError_t e = launch_fused_z(n, fa, bp.tw_full, p->stream);
                     if (e != hipSuccess) return e;
                     if (yx_inv_supported(n, lay == 1)) {
-                        InvArgs ia = inv_args(bp, 8, 0, 1, lay == 1);
+                        InvArgs ia = inv_args(bp, 8, 0, 1, lay == 1, halves);
                         ia.out[0] = p->scratch_real;
                         return launch_yx_inv(n, false, ia, p->stream);
                     }
-                    e = inv_y_fused(n, bp.acc, bp.tw_full, bp.split_tab, bp.part, r != 0, p->stream);
+                    e = inv_y_fused(n, bp.acc, bp.tw_full, bp.split_tab, bp.part, r != 0, halves, p->stream);
                     if (e != hipSuccess) return e;
                     return launch_x_inv(n, false, bp.acc, p->scratch_real, false, bp.tw_half, bp.twist, 1.0, nullptr,
                                         p->stream);
@@ -1211,9 +1215,11 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
             fa.ring = bp.head;
             fa.frozen = frozen;
             fa.sk = bp.sk; fa.g0 = bp.ghat0; fa.inv_n3 = inv_n3; fa.mu = bp.mu;
+            bool halves = false;
+            fa.halves = &halves;
             HIPCHK(launch_fused_z(n, fa, bp.tw_full, st));
             if (yx_inv_supported(n, bp.parity())) {
-                InvArgs ia = inv_args(bp, cs, b, nb, bp.parity());
+                InvArgs ia = inv_args(bp, cs, b, nb, bp.parity(), halves);
                 ia.out_f64 = out_f64;
                 for (int j = 0; j < nb; ++j) ia.out[j] = outp[b + j - b0];
                 HIPCHK(launch_yx_inv(n, false, ia, st));
@@ -1223,7 +1229,7 @@ static int field_box(lc_plan_t *p, int box, int b0, int b1, void *const *outp, b
             for (int j = 0; j < nb; ++j) {
                 char *acc = bp.acc + (size_t)(b + j) * se * cs;
                 char *part = bp.part + (size_t)j * bp.part_stride * 8;
-                HIPCHK(inv_y_fused(n, acc, bp.tw_full, tab, part, fa.rounds != 0, st));
+                HIPCHK(inv_y_fused(n, acc, bp.tw_full, tab, part, fa.rounds != 0, halves, st));
                 HIPCHK(launch_x_inv(n, false, acc, outp[b + j - b0], out_f64, bp.tw_half, bp.twist, inv_n3,
                                     bp.mu + b + j, st));
             }
@@ -1671,7 +1677,7 @@ int lc_time_kernel(lc_plan_t *p, int32_t box, int32_t kernel, int32_t reps, doub
             }
             case LC_KERNEL_COL_Z_INV: return launch_col(n, p->t_f64, 2, false, acc0, bp.tw_full, st);
             case LC_KERNEL_COL_Y_INV:
-                return fused ? inv_y_fused(n, acc0, bp.tw_full, bp.split_tab, bp.part, bp.fused_rounds != 0, st)
+                return fused ? inv_y_fused(n, acc0, bp.tw_full, bp.split_tab, bp.part, bp.fused_rounds != 0, false, st)
                              : launch_col(n, p->t_f64, 1, false, acc0, bp.tw_full, st);
             case LC_KERNEL_YX_INV: {
                 InvArgs ia = inv_args(bp, cs, 0, 1, true);

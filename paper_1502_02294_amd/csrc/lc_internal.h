@@ -71,7 +71,7 @@ int xy_first_parity(int n);   // first parity-layout shape, -1 if none
 // U_1 = W_N^-q (T[q] - T[q+N/2]); N = 192, 256), or whole planes (N = 64, 96,
 // 128): out[b] = IDFT(acc + b acc_stride) * scale + mu[b], N^3 reals (FP32 or
 // FP64). With part non-null (FP32) the second parts of split fused tiles
-// (split_tab) are added.
+// (split_tab; null: every tile, slot = tile) are added.
 struct InvArgs {
     static constexpr int kMax = 4;
     const void *acc;
@@ -155,6 +155,10 @@ struct FusedArgs {
     const double *sk = nullptr, *g0 = nullptr;
     double inv_n3 = 0.0;
     double *mu = nullptr;
+    // non-null: a rounds launch over few tiles may split each tile's slices in
+    // two, setting *halves: the inverse y pass then adds every tile's part
+    // (slot = tile, no split table)
+    bool *halves = nullptr;
 };
 int fused_variants(int n);   // number of register schedules compiled for n
 bool fused_parity_supported(int n);   // parity-layout input compiled for n
@@ -179,7 +183,8 @@ int64_t fused_tiles(int n);  // column tiles of the fused pass (main + nyq)
 int fused_cpw(int n);        // columns per tile
 
 // Inverse y pass of an accumulator whose fused z pass split some tiles: the
-// second parts (split_tab, part) are added while loading. FP32 only.
+// second parts (split_tab, part; a null table: every tile's, slot = tile) are
+// added while loading. FP32 only.
 hipError_t launch_col_y_inv_combine(int n, void *spec, const void *tw_full, const int *split_tab,
                                     const void *part, hipStream_t st);
 

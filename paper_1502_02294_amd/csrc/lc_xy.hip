@@ -401,15 +401,15 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
 //      Z[p] = E'_p + i O'_p of the half-length trick, then the N/2-point
 //      inverse transform), scaled by 1/N^3, plus the FP64 mean, and stored.
 // With COMBINE the second parts of tiles that the fused pass split between
-// two workgroups (tab, part) are added while loading.
+// two workgroups (part; 1: of the tiles in tab, 2: of every tile) are added
+// while loading.
 // At 128^3 the separate passes took 7.2 + 8.4 us a band, this one 12.1 us;
 // two bands of 96^3 22 us in four launches, 11.8 us in one.
-template <typename T, int N, int NR_, typename TOUT, bool S8, int NB_, bool COMBINE>
+template <typename T, int N, int NR_, typename TOUT, bool S8, int NB_, int COMBINE>
 __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, NR_>::NT)) void yx_inv_kernel(
     const cx<T> *__restrict__ acc0, int64_t acc_stride, OutTab outs, const cx<T> *__restrict__ tw_half,
     const cx<T> *__restrict__ twist, const cx<T> *__restrict__ tw_full, double scale, const double *__restrict__ mu,
-    const int *__restrict__ tab, const cx<T> *__restrict__ part0, int64_t part_stride, int cpw_z,
-    int64_t tiles_main) {
+    const int *__restrict__ tab, const cx<T> *__restrict__ part0, int64_t part_stride) {
     using SH = XYShape<T, N, S8, NB_, 0, NR_>;
     constexpr int L = SH::L, NR = SH::NR, TX = SH::TX, TY = SH::TY, NB = SH::NB, RPB = SH::RPB, CPB = SH::CPB;
     constexpr int NT = SH::NT, SK = SH::SK, LSX = SH::LSX, HALVES = SH::HALVES;
@@ -437,11 +437,14 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, NR_>::NT)) void yx_inv_k
     const cx<T> *__restrict__ mainp = acc + ((int64_t)z * N + sp * NR) * L;
     const cx<T> *__restrict__ nyq = acc + spec_main(N) + (int64_t)z * N + sp * NR;
 
-    // every column batch of the half plane, loaded up front
+    // every column batch of the half plane, loaded up front (the tiles' width
+    // is a constant: divisions by a variable one took longer than the loads)
+    constexpr int CZ = fused_cols<N>(), TMAIN = N * (N / 2) / CZ;
     cx<T> yr[NB][EYN];
-    auto part_at = [&](int64_t zt, int zc) -> cx<T> {
+    auto part_at = [&](int zt, int zc) -> cx<T> {
+        if constexpr (COMBINE == 2) return part[((int64_t)zt * N + z) * CZ + zc];
         const int w = tab[zt];
-        return w >= 0 ? part[((int64_t)w * N + z) * cpw_z + zc] : mk((T)0, (T)0);
+        return w >= 0 ? part[((int64_t)w * N + z) * CZ + zc] : mk((T)0, (T)0);
     };
     static_for<NB>([&](auto cbc) {
         constexpr int cb = decltype(cbc)::value;
@@ -451,18 +454,17 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, 0, NR_>::NT)) void yx_inv_k
             const int r = EY::in_pos(yt, e);
             if (p != 0) {
                 cx<T> v = mainp[(int64_t)r * L + p];
-                if constexpr (COMBINE) {
-                    const int64_t cc = (int64_t)(sp * NR + r) * L + p;
-                    v = v + part_at(cc / cpw_z, (int)(cc % cpw_z));
+                if constexpr (COMBINE != 0) {
+                    const int cc = (sp * NR + r) * L + p;
+                    v = v + part_at(cc / CZ, cc % CZ);
                 }
                 yr[cb][e] = v;
             } else {
                 cx<T> a = mainp[(int64_t)r * L], b = nyq[r];
-                if constexpr (COMBINE) {
-                    const int64_t cc = (int64_t)(sp * NR + r) * L;
-                    a = a + part_at(cc / cpw_z, (int)(cc % cpw_z));
-                    const int q = sp * NR + r;
-                    b = b + part_at(tiles_main + q / cpw_z, q % cpw_z);
+                if constexpr (COMBINE != 0) {
+                    const int q = sp * NR + r, cc = q * L;
+                    a = a + part_at(cc / CZ, cc % CZ);
+                    b = b + part_at(TMAIN + q / CZ, q % CZ);
                 }
                 yr[cb][e] = mk(a.x - b.y, a.y + b.x);   // a + i b
             }
@@ -535,23 +537,27 @@ bool yx_inv_supported(int n, bool parity) {
 template <typename T, int N, int NR, bool S8, int NB>
 static hipError_t yx_inv_t(const InvArgs &a, hipStream_t st) {
     using SH = XYShape<T, N, S8, NB, 0, NR>;
-    const int cpw = fused_cpw(N);
-    const int64_t tiles_main = (int64_t)N * (N / 2) / cpw;
     const dim3 grid((unsigned)(N * (N / NR) * a.nband));
     OutTab outs;
     for (int b = 0; b < a.nband; ++b) outs.p[b] = a.out[b];
 #define YI_(TOUT, COMB)                                                                                            \
     hipLaunchKernelGGL((yx_inv_kernel<T, N, NR, TOUT, S8, NB, COMB>), grid, dim3(SH::NT), 0, st,                   \
                        (const cx<T> *)a.acc, a.acc_stride, outs, (const cx<T> *)a.tw_half, (const cx<T> *)a.twist, \
-                       (const cx<T> *)a.tw_full, a.scale, a.mu, a.split_tab, (const cx<T> *)a.part, a.part_stride, \
-                       cpw, tiles_main)
+                       (const cx<T> *)a.tw_full, a.scale, a.mu, a.split_tab, (const cx<T> *)a.part, a.part_stride)
     if constexpr (sizeof(T) == 4) {
-        if (a.part) {
-            if (a.out_f64) YI_(double, true); else YI_(float, true);
+        if (a.part && a.split_tab) {
+            if (a.out_f64) YI_(double, 1); else YI_(float, 1);
             return hipGetLastError();
         }
+        if constexpr (N <= 96) {
+            if (a.part) {
+                if (a.out_f64) YI_(double, 2); else YI_(float, 2);
+                return hipGetLastError();
+            }
+        }
+        if (a.part) return hipErrorInvalidValue;
     }
-    if (a.out_f64) YI_(double, false); else YI_(float, false);
+    if (a.out_f64) YI_(double, 0); else YI_(float, 0);
 #undef YI_
     return hipGetLastError();
 }
