@@ -51,6 +51,17 @@ template <typename T> struct FusedDev {
     int32_t frozen;            // >= 0: every lookback slice reads slot `frozen` (instantaneous field)
 };
 
+// a complex value of a slice spectrum, with a non-temporal load for NT
+template <bool NT, typename T> __device__ __forceinline__ cx<T> ld_spec(const char *p) {
+    if constexpr (NT) {
+        typedef T v2 __attribute__((ext_vector_type(2)));
+        const v2 v = __builtin_nontemporal_load((const v2 *)p);
+        return mk(v[0], v[1]);
+    } else {
+        return *(const cx<T> *)p;
+    }
+}
+
 // p-blocks of CPW columns whose octant rows share a 128-byte line
 __host__ __device__ constexpr int fused_gp(int cpw, int tsize) {
     return cpw * tsize >= 128 ? 1 : 128 / (cpw * tsize);
@@ -146,6 +157,7 @@ __device__ __forceinline__ void fused_walk(const FusedDev<T> &a, const ColSet &s
 // input element is read once for both, and both go through the z transform,
 // the kernel product and the sum. Output o of a column is at
 // o * (N/2 rows) after the first; a second part goes to part slot 2 w + o.
+// NTL: the spectra are read with non-temporal loads.
 // KS: sums in FP64 (the FP32 form with one or two bands per launch; three or
 // four bands sum in FP32: their sums would not fit in registers otherwise). A
 // product and sum is a conversion and one FP64 instruction per value, where a
@@ -153,7 +165,7 @@ __device__ __forceinline__ void fused_walk(const FusedDev<T> &a, const ColSet &s
 // of 64^3 24.3 -> 23.1 us, two of 21 slices of 96^3 65 -> 61.5), and the
 // sum's error is that of its inputs. The plain forms (T = double, or float) sum
 // in T in the order of the slices.
-template <typename T, int L, int NB_, typename S, int PF, int IN, bool KS>
+template <typename T, int L, int NB_, typename S, int PF, int IN, bool KS, bool NTL = false>
 __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(FusedDev<T> a, ColSet s0, ColSet s1,
                                                                            const cx<T> *__restrict__ tw_g) {
     // input: 0 y-transformed slices, 1 the same in the parity layout, 2
@@ -272,7 +284,7 @@ __global__ __launch_bounds__((FusedShape<T, L, S>::NT)) void fused_z_kernel(Fuse
         const uint32_t xoff0 = (uint32_t)((in0 + (int64_t)rowpos(0) * in_rs) * CB);
         const int64_t rsb = in_rs * CB;
         auto xld = [&](const char *base, int e) {
-            return *(const cx<T> *)(base + (int64_t)(rowpos(e) - rowpos(0)) * rsb + xoff0);
+            return ld_spec<NTL, T>(base + (int64_t)(rowpos(e) - rowpos(0)) * rsb + xoff0);
         };
         constexpr bool GFULL = GROWS * RSTEP <= HP;   // every thread's last row exists
         const int rlast = t + (GROWS - 1) * RSTEP;
@@ -585,16 +597,6 @@ template <int LANES> __device__ __forceinline__ void lane_swap(cx<float> &a, cx<
 // per slice).
 __device__ __forceinline__ void keep32(uint32_t &v) { asm volatile("" : "+v"(v)); }
 
-template <bool NT> __device__ __forceinline__ cx<float> ld_spec(const char *p) {
-    if constexpr (NT) {
-        typedef float f2v __attribute__((ext_vector_type(2)));
-        const f2v v = __builtin_nontemporal_load((const f2v *)p);
-        return mk(v[0], v[1]);
-    } else {
-        return *(const cx<float> *)p;
-    }
-}
-
 template <int L> struct LaneTw {
     cx<float> mid[8], last[8];   // forward twiddles: middle pass (q, r at q RM + r), last pass (r)
 };
@@ -755,7 +757,7 @@ __global__ __launch_bounds__((LaneShape<L>::NT)) void fused_lane_kernel(FusedDev
 #pragma unroll
             for (int o = 0; o < NO; ++o)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xn[o][e] = ld_spec<NT_>(src + o * obytes + e * rsb + off);
+                for (int e = 0; e < 8; ++e) xn[o][e] = ld_spec<NT_, float>(src + o * obytes + e * rsb + off);
         };
         float gv[NB_][NO][8], gw[NB_];
         auto load_g = [&](int k) {
@@ -1003,6 +1005,11 @@ static hipError_t fused_launch(const FusedArgs &fa, const void *tw, hipStream_t 
         else return hipErrorInvalidValue;
     }
     if (fa.nband == 2) GO_(2);
+    // (non-temporal loads beyond the last-level cache, as in fused_lane_launch)
+    if constexpr (N == 192)
+        if ((fa.frozen >= 0 ? 1 : kmax) * fa.spec_stride * 8 > ((int64_t)256 << 20))
+            return fused_go<N, SH::CPW, SH::NT, IN == 1, fused_z_kernel<float, N, 1, S, PF, IN, true, true>>(
+                fa, tw, st, s0, s1, tiles, kmax);
     GO_(1);
 #undef GO_
 }
@@ -1125,9 +1132,19 @@ static hipError_t fused_plain_t(const FusedArgs &fa, const void *tw, hipStream_t
     d.acc = (cx<T> *)fa.acc; d.acc_stride = fa.acc_stride;
     d.kmax = kmax; d.P = (int32_t)tiles; d.W = tiles * kmax;
     d.rounds = 1; d.tiles = tiles; d.K = fa.K; d.ring = fa.ring; d.frozen = fa.frozen;
+    // (beyond the last-level cache the spectra stream past it, as in
+    // fused_lane_launch)
+    const bool nt = SH::CPW * sizeof(cx<T>) >= 128 &&
+                    (fa.frozen >= 0 ? 1 : kmax) * fa.spec_stride * (int64_t)sizeof(cx<T>) > ((int64_t)256 << 20);
 #define FP_(NB, IN)                                                                                               \
-    hipLaunchKernelGGL((fused_z_kernel<T, N, NB, S, 1, IN, false>), dim3((unsigned)tiles), dim3(SH::NT), 0, st, d, s0, \
-                       s1, (const cx<T> *)tw)
+    do {                                                                                                          \
+        if (nt)                                                                                                   \
+            hipLaunchKernelGGL((fused_z_kernel<T, N, NB, S, 1, IN, false, true>), dim3((unsigned)tiles), dim3(SH::NT), \
+                               0, st, d, s0, s1, (const cx<T> *)tw);                                              \
+        else                                                                                                      \
+            hipLaunchKernelGGL((fused_z_kernel<T, N, NB, S, 1, IN, false>), dim3((unsigned)tiles), dim3(SH::NT), 0, st, \
+                               d, s0, s1, (const cx<T> *)tw);                                                     \
+    } while (0)
     if constexpr (fused_par<N>()) {
         if (fa.parity) {
             if (fa.nband == 2) FP_(2, 1);
