@@ -212,10 +212,13 @@ __device__ double cell_exact(const ExactShell &e, const GaussRule &g, double x0,
 // however many shells the batch holds. Arithmetic bound (FP64 pow, exp and
 // sqrt per subpoint). One launch per shell, every cell testing every image,
 // took 220 us a shell at 128^3 (24 shells, m = 4); the batches take 11.6 us.
-// The group adds to G[k][cell] itself, which no other group touches: no
-// atomics, and the result does not depend on timing. LPC = 8 spreads the m^3
-// subpoints of a cell over eight lanes (m = 1 has one, the exact rule works
-// cell by cell: LPC = 1).
+// G is the same for every order of a cell's three indices (cubic box, cells and
+// subpoints), so only cells ci <= cj <= ck are summed, a sixth of them, and the
+// sum goes to the up to six cells of the other orders: 11.6 us a shell without
+// this, 4.0 us with. A group adds to these cells itself, which no other group
+// touches: no atomics, and the result does not depend on timing. LPC = 8
+// spreads the m^3 subpoints of a cell over eight lanes (m = 1 has one, the
+// exact rule works cell by cell: LPC = 1).
 template <int LPC, bool EXACT>
 __global__ __launch_bounds__(256) void greens_shells_kernel(ShellArgs a) {
     constexpr int KM = ShellArgs::kMax;
@@ -243,9 +246,22 @@ __global__ __launch_bounds__(256) void greens_shells_kernel(ShellArgs a) {
     const int64_t cells = (int64_t)H * H * H;
     const int64_t cell = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPC;
     const int sub = threadIdx.x % LPC;
-    if (cell >= cells) return;   // (a whole group leaves together)
     const int ci = (int)(cell / ((int64_t)H * H)), cj = (int)((cell / H) % H), ck = (int)(cell % H);
-    double *__restrict__ G = a.oct + cell;
+    if (cell >= cells || ci > cj || cj > ck) return;   // (a whole group leaves together)
+    // add v to the cells of slice k with these indices in any order: order o of
+    // (ci, cj, ck), ikj, jik, jki, kij, kji, those that differ
+    double *__restrict__ G = a.oct;
+    const int orders = ci == ck ? 0x01 : ci == cj ? 0x13 : cj == ck ? 0x0D : 0x3F;
+    auto add = [&](int k, double v) {
+#pragma unroll
+        for (int o = LPC == 1 ? 0 : sub; o < 6; o += LPC) {
+            if (!(orders >> o & 1)) continue;
+            const int x = o < 2 ? ci : o < 4 ? cj : ck;
+            const int y = o == 0 || o == 5 ? cj : o == 1 || o == 3 ? ck : ci;
+            const int z = ci + cj + ck - x - y;
+            G[k * cells + ((int64_t)x * H + y) * H + z] += v;
+        }
+    };
     const int m = a.m, m3 = m * m * m;
     const double l = a.l, r_lo = r[0], r_hi = r[cnt];
     const double four_pi = 12.566370614359172954;
@@ -285,7 +301,7 @@ __global__ __launch_bounds__(256) void greens_shells_kernel(ShellArgs a) {
                 while (kb + 1 < cnt && r[kb + 1] <= dmax + margin) ++kb;
                 if constexpr (EXACT) {
                     for (int k = ka; k <= kb; ++k)
-                        if (sh[k].pref != 0.0) G[k * cells] += cell_exact(sh[k], rule16, lo0, hi0, lo1, hi1, lo2, hi2);
+                        if (sh[k].pref != 0.0) add(k, cell_exact(sh[k], rule16, lo0, hi0, lo1, hi1, lo2, hi2));
                 } else {
                     if (a.self_pair && x0 == 0 && x1 == 0 && x2 == 0) {
                         // the source's own cell belongs to slice 0
@@ -320,11 +336,9 @@ __global__ __launch_bounds__(256) void greens_shells_kernel(ShellArgs a) {
                             acc1 += __shfl_xor(acc1, o, 64);
                             acc2 += __shfl_xor(acc2, o, 64);
                         }
-                        if (sub == 0) {
-                            if (acc0 != 0.0) G[kk * cells] += acc0;
-                            if (acc1 != 0.0) G[(kk + 1) * cells] += acc1;
-                            if (acc2 != 0.0) G[(kk + 2) * cells] += acc2;
-                        }
+                        if (acc0 != 0.0) add(kk, acc0);
+                        if (acc1 != 0.0) add(kk + 1, acc1);
+                        if (acc2 != 0.0) add(kk + 2, acc2);
                     }
                 }
             }
