@@ -3,8 +3,7 @@
 
 One step = the whole path over one batch of synthetic input: every slice's
 source grid (already resident in HBM) is staged and transformed, and the
-field of every band is evaluated (lc_step, replayed from a captured HIP
-graph). Kernel construction is precomputation and is timed separately.
+field of every band is evaluated (lc_step). Kernel construction is precomputation and is timed separately.
 
 Prints ONE JSON line. Headline workload: 256^3 grid, 200 Mpc box, 40 slices
 of 5 Mpc, FP32 form (FP64 slice sum, mean and kernels); the plain FP64
@@ -79,10 +78,10 @@ def compulsory_bytes(n, K, B, rsz=4):
     return n ** 3 * K * rsz + oct_bytes(n, rsz) * K * B + n ** 3 * rsz * B
 
 
-def bytes_model(n, K, B, fused, csz, rsz):
-    """Bytes each kernel launch moves in the implemented passes (FP32:
-    csz=8, rsz=4); B = bands handled per launch."""
-    n3 = n ** 3
+def bytes_model(n, K, B):
+    """Bytes each kernel launch of the FP32 form moves in the implemented
+    passes; B = bands handled per launch."""
+    n3, csz, rsz = n ** 3, 8, 4
     spec = n * n * (n // 2 + 1) * csz
     octb = oct_bytes(n, rsz)
     m = {
@@ -93,12 +92,7 @@ def bytes_model(n, K, B, fused, csz, rsz):
         "x_inv": spec + n3 * rsz,             # read spectrum, write the field
         "yx_inv": spec + n3 * rsz,            # fused inverse y + x (parity layout): read A, write the field
     }
-    if fused:
-        m["fused_z"] = K * (spec + octb * B) + B * spec   # every slice + its kernel octants, write A once
-    else:
-        m["col_z_fwd"] = 2 * spec
-        m["mac"] = spec + octb + 2 * spec               # read S^, G^, read-modify-write A
-        m["col_z_inv"] = 2 * spec
+    m["fused_z"] = K * (spec + octb * B) + B * spec   # every slice + its kernel octants, write A once
     return m
 
 
@@ -173,7 +167,7 @@ def per_step_times(torch, plan, grids, outs, steps):
 
 
 def run_form(lc, torch, boxes, grids, precision, steps, warmup, time_kernels=True):
-    """Build, then time `steps` graph-replayed lc_step calls over all boxes."""
+    """Build, then time `steps` lc_step calls over all boxes."""
     fused = precision == lc.LC_PREC_FP32
     plan = lc.Plan(boxes, precision=precision, use_graph=True, autotune=fused)
     torch.cuda.synchronize()
@@ -189,13 +183,13 @@ def run_form(lc, torch, boxes, grids, precision, steps, warmup, time_kernels=Tru
            "step_ms": per_step_times(torch, plan, grids, outs, steps),
            "value": cells / (ms * 1e-3), "schedule": plan.get_schedule(0)}
     if time_kernels:
-        res["kernels"] = kernel_times(lc, plan, boxes[0], precision, ms)
+        res["kernels"] = kernel_times(lc, plan, boxes[0], ms)
     return res, outs, plan
 
 
-def kernel_times(lc, plan, box, precision, ms):
+def kernel_times(lc, plan, box, ms):
+    """Kernels of an FP32-form step, each timed alone (lc_time_kernel)."""
     K, B, n = box.n_slices, len(box.bands), box.n
-    fused = precision == lc.LC_PREC_FP32
     sched = plan.get_schedule(0)
     group = 1
     if sched["xy_variant"] >= 0:
@@ -214,16 +208,10 @@ def kernel_times(lc, plan, box, precision, ms):
     except lc.LCError:
         ids.update({"col_y_inv": lc.LC_KERNEL_COL_Y_INV, "x_inv": lc.LC_KERNEL_X_INV})
         per_step.update({"col_y_inv": B, "x_inv": B})
-    if fused:
-        ids["fused_z"] = lc.LC_KERNEL_FUSED_Z
-        per_step["fused_z"] = (B + 1) // 2
-    else:
-        ids.update({"col_z_fwd": lc.LC_KERNEL_COL_Z_FWD, "mac": lc.LC_KERNEL_MAC,
-                    "col_z_inv": lc.LC_KERNEL_COL_Z_INV})
-        per_step.update({"col_z_fwd": K, "mac": K * B, "col_z_inv": B})
-    csz, rsz = (16, 8) if precision == lc.LC_PREC_FP64 else (8, 4)
-    bl = min(B, 2) if fused else 1
-    model = bytes_model(n, K, bl, fused, csz, rsz)
+    ids["fused_z"] = lc.LC_KERNEL_FUSED_Z
+    per_step["fused_z"] = (B + 1) // 2
+    rsz, bl = 4, min(B, 2)
+    model = bytes_model(n, K, bl)
     model["xy_fwd"] *= group
     kern = {}
     for name, kid in ids.items():
@@ -610,7 +598,7 @@ def main():
     kd = kern[dom]
     achieved = step_comp / (ms * 1e-3) / 1e9
     line["roofline"] = {
-        "bound": "hbm", "kernel": "whole step (one lc_step graph replay)",
+        "bound": "hbm", "kernel": "whole step (one lc_step)",
         "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
         "traffic": step_traffic,
         "algorithmic_bytes": step_comp,
@@ -642,13 +630,11 @@ def main():
     if not args.no_fp64:
         g64 = [torch.from_numpy(h).cuda() for h in host]
         log("fp64 plain method: build + timed steps")
-        r64, out64, plan64 = run_form(lc, torch, [box], g64, lc.LC_PREC_FP64, args.fp64_steps, 1)
+        r64, out64, plan64 = run_form(lc, torch, [box], g64, lc.LC_PREC_FP64, args.fp64_steps, 1, time_kernels=False)
         plan64.close()
         del plan64
         log(f"fp64 {r64['ms_per_step']:.3f} ms/step")
-        line["fp64_plain"] = {"value": r64["value"], "ms_per_step": r64["ms_per_step"],
-                              "kernels": {k: {"avg_ms": round(v["avg_ms"], 5), "pass_GBps": round(v["pass_GBps"], 1)}
-                                          for k, v in r64["kernels"].items()}}
+        line["fp64_plain"] = {"value": r64["value"], "ms_per_step": r64["ms_per_step"]}
         line["speedup_vs_fp64_plain"] = r32["value"] / r64["value"]
         d = (out32[0].double() - out64[0])
         line["fp32_vs_fp64_gpu"] = {

@@ -67,11 +67,11 @@ typedef enum {
 
 /* Arithmetic of the transforms and the slice sum. */
 typedef enum {
-    /* FP64 everywhere; unfused passes (forward x, y, z per slice, then a
-     * separate multiply-accumulate over slices, then one inverse). */
+    /* FP64 everywhere: the passes of LC_PREC_FP32 in FP64, one launch shape
+     * per N, the slices summed in order. */
     LC_PREC_FP64 = 0,
     /* FP32 everywhere, twiddles computed in FP32, plain FP32 slice sum,
-     * same unfused passes as LC_PREC_FP64. */
+     * same passes as LC_PREC_FP64. */
     LC_PREC_FP32_PLAIN = 1,
     /* FP32 butterflies with twiddles generated in FP64; the forward z
      * transform, the multiply-accumulate over slices (summed in FP64 with
@@ -196,8 +196,7 @@ int lc_build_greens(lc_plan_t *plan, int32_t box, int32_t band, const lc_atten *
 
 /* Stage slice k of a box - algorithm step 4 up to the passes that do not
  * depend on the kernel: deposit (point list) or read (dense grid), then the
- * forward transform (x and y passes for LC_PREC_FP32, all three passes for
- * the unfused forms). Replaces whatever the slice held; slices never
+ * forward transform (x and y passes; all three with spectra_3d). Replaces whatever the slice held; slices never
  * pushed are zero. */
 int lc_push_sources(lc_plan_t *plan, int32_t box, int32_t slice, const lc_sources *src);
 
@@ -348,8 +347,9 @@ void lc_destroy(lc_plan_t *plan);
  * library call on this thread. Never NULL. */
 const char *lc_last_error(void);
 
-/* Largest |Im G^| / max|G^| seen by lc_build_greens for (box, band) (the
- * kernel spectrum is real up to rounding); synchronises the stream. */
+/* Largest |Im G^| / max|G^| of the last lc_build_greens for (box, band): 0,
+ * since the builder transforms the real, even kernel by cosine transforms;
+ * synchronises the stream. */
 int lc_greens_imag_ratio(lc_plan_t *plan, int32_t box, int32_t band, double *ratio);
 
 /* Copy G^_{k,b}(0) = sum_c G_{k,b}(c) (FP64) for all K slices to host
@@ -360,12 +360,14 @@ int lc_greens_dc(lc_plan_t *plan, int32_t box, int32_t band, double *dc);
 typedef enum {
     LC_KERNEL_X_FWD = 0,      /* forward x pass of one slice (reads the source grid) */
     LC_KERNEL_COL_Y_FWD = 1,  /* forward y pass of one slice, in place               */
-    LC_KERNEL_COL_Z_FWD = 2,  /* forward z pass of one slice (unfused forms)          */
+    LC_KERNEL_COL_Z_FWD = 2,  /* forward z pass of one slice (plain forms; not part of
+                                 a step, which transforms along z in the slice sum)    */
     LC_KERNEL_FUSED_Z = 3,    /* fused z pass + slice sum over all slices (FP32 form)  */
-    LC_KERNEL_MAC = 4,        /* plain multiply-accumulate of one slice (unfused)     */
-    LC_KERNEL_COL_Z_INV = 5,  /* inverse z pass of one band (unfused forms)           */
+    LC_KERNEL_MAC = 4,        /* slice sum over one slice (plain forms)               */
+    LC_KERNEL_COL_Z_INV = 5,  /* inverse z pass of one band (plain forms; as 2)       */
     LC_KERNEL_COL_Y_INV = 6,  /* inverse y pass of one band                           */
-    LC_KERNEL_X_INV = 7,      /* inverse x pass + epilogue of one band                */
+    LC_KERNEL_X_INV = 7,      /* inverse x pass + epilogue of one band (6 and 7: at
+                                 N = 64, 96, 128 a step fuses them)                    */
     LC_KERNEL_XY_FWD = 8,     /* fused forward x + y pass of one slice (FP32 form,
                                  N in {64, 96, 128, 192, 256}, where the step uses it
                                  in place of LC_KERNEL_X_FWD + LC_KERNEL_COL_Y_FWD)   */
@@ -398,7 +400,7 @@ typedef enum {
  *                  in FP64; with 3 or 4 (N = 384, 512) it is a plain
  *                  FP32 sum. Default n_fused_bands; not tuned.
  *   spectra_3d     1: the slice spectra are stored transformed along z as
- *                  well (3D spectra, as in the plain forms): each push adds
+ *                  well (3D spectra): each push adds
  *                  the z pass, and a field is the product with G^ and the
  *                  sum over slices alone, then one inverse per band (the
  *                  regime of a rolling light-cone, where each observing

@@ -634,8 +634,11 @@ int autotune_box_uncached(lc_plan_t *p, BoxPlan &bp) {
     int fz_v[2] = {bp.fused_variant, bp.fused_variant}, fz_r[2] = {bp.fused_rounds, bp.fused_rounds};
     for (int lay = 0; lay < 2; ++lay) {
         if (!fwd_seen[lay]) continue;
-        for (int v = 0; v < fused_variants(n); ++v)
+        // (the lane-exchange variant, the last where it exists, is the preferred one)
+        const int nv = fused_variants(n);
+        for (int i = 0; i < nv; ++i)
             for (int r = 1; r >= 0; --r) {
+                const int v = nv > 4 ? nv - 1 - i : i;
                 bp.fused_variant = v;
                 bp.fused_rounds = r;
                 FusedArgs fa = fused_args(bp);
@@ -1592,6 +1595,7 @@ int lc_greens_imag_ratio(lc_plan_t *p, int32_t box, int32_t band, double *ratio)
     BoxPlan &bp = p->boxes[box];
     if (band < 0 || band >= bp.B) return fail(LC_EINVAL, "band out of range");
     if (!bp.built[band]) return fail(LC_ESTATE, "kernel not built");
+    HIPCHK(hipStreamSynchronize(p->stream));
     // the builder takes the spectrum of the real, even kernel by cosine
     // transforms: no imaginary part arises
     *ratio = 0.0;
