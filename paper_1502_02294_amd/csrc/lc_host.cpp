@@ -1048,6 +1048,14 @@ static int push_point_rows(lc_plan_t *p, BoxPlan &bp, const lc_sources *srcs, in
     t.rows = (double *)(p->scratch_real + t.count * n2 * 4);
     HIPCHK(launch_point_rows(t, st));
     SrcTab tab;
+    // Spectra of a whole step well beyond the last-level cache (256 MB) are
+    // stored past it. Point-list steps, cached -> non-temporal stores: 256^3 x 40
+    // (2.7 GB) 2255 -> 2073 us, FP64 x 16 (2.2 GB) 1642 -> 1559, x 16 (1.1 GB) 800
+    // -> 780, 192^3 x 24 (690 MB) 682 -> 660; at 256^3 x 8 (540 MB) 441 -> 445, at
+    // 192^3 x 12 (340 MB) equal, at 128^3 x 24 (200 MB) 150 -> 161. Dense grids,
+    // read as fast as the spectra are written, lose by it at every size (256^3 x
+    // 40: 1975 -> 2066).
+    tab.stream = most > 1 && bp.K * spec_elems(n) * (p->t_f64 ? 16 : 8) > ((int64_t)640 << 20);
     for (int j = 0; j < t.count; ++j) {
         tab.p[j] = t.map + j * n2;
         bp.last_src[slot + j] = nullptr;

@@ -31,6 +31,7 @@ int x_pass_wgs(int n);
 struct SrcTab {
     static constexpr int kMax = 64;
     const void *p[kMax];
+    int32_t stream = 0;   // compact rows: spectra stored past the last-level cache
 };
 
 // Forward x pass of `count` slices: slice i reads in.p[i] and writes the

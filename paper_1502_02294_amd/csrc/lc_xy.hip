@@ -145,8 +145,17 @@ __device__ __forceinline__ void pin(cx<float> &v) { asm volatile("" : "+v"(v.x),
 __device__ __forceinline__ void pin(cx<double> &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 __device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }
 
+template <typename T> __device__ __forceinline__ void st_stream(cx<T> *p, cx<T> v) {
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    v2 w;
+    w[0] = v.x;
+    w[1] = v.y;
+    __builtin_nontemporal_store(w, (v2 *)p);
+}
+
 // ROWS: the FP64 input comes as compact rows (point lists): srcs.p[slice] is
-// the slice's row map, rows the cells; an empty row is read as zeros.
+// the slice's row map, rows the cells; an empty row is read as zeros. Its
+// launches are bound by their stores; srcs.stream makes them non-temporal.
 template <typename T, int N, int NR_, typename TIN, bool S8, int NB_, int NC_, bool PER, bool ROWS>
 __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd_kernel(
     SrcTab srcs, cx<T> *__restrict__ spec0, int64_t spec_stride, const cx<T> *__restrict__ tw_half,
@@ -333,7 +342,10 @@ __global__ __launch_bounds__((XYShape<T, N, S8, NB_, NC_, NR_>::NT)) void xy_fwd
             for (int e = 0; e < EYN; ++e) y[e] = reg[EY::in_pos(yt, e) * ES + yc];
             EY::run(y, reg, yc, ES, yt, twy);
             const int p = cb * CPB + yc;
-            if (p != 0) {
+            if (ROWS && srcs.stream && p != 0) {
+#pragma unroll
+                for (int e = 0; e < EYN; ++e) st_stream(mainp + (int64_t)EY::out_pos(yt, e) * L + p, y[e]);
+            } else if (p != 0) {
 #pragma unroll
                 for (int e = 0; e < EYN; ++e) mainp[(int64_t)EY::out_pos(yt, e) * L + p] = y[e];
             } else {

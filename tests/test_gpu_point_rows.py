@@ -80,3 +80,31 @@ def test_point_rows_equal_dense_grids(n, form):
         assert err.value.code == lc.LC_ENONFINITE
         del keep
     plan.close()
+
+
+@pytest.mark.parametrize("n,K", [(192, 24), (256, 10)])
+def test_point_rows_stored_past_the_cache(n, K):
+    """FP32 steps whose spectra are stored non-temporally (more than 640 MiB):
+    bit for bit the field of dense FP64 grids, on two passes."""
+    import paper_1502_02294_amd as lc
+    L = 0.78125 * n
+    box = li.Box(n=n, box=L, radii=np.linspace(0.0, 0.9 * L, K + 1), supersample=1, bands=[li.Atten()],
+                 sources=[None] * K)
+    plan = lc.Plan([box], precision=lc.LC_PREC_FP32)
+    plan.build_all()
+    for seed in (1, 2):
+        rng = np.random.default_rng([seed, n])
+        dev = []
+        for k in range(K):
+            cells = rng.integers(0, n ** 3, size=300 * k)
+            lum = rng.integers(1, 9, size=300 * k).astype(np.float64)
+            g = torch.zeros(n ** 3, dtype=torch.float64, device="cuda")
+            g.index_add_(0, torch.from_numpy(cells).cuda(), torch.from_numpy(lum).cuda())
+            plan.push_grid(0, k, g)
+            dev.append((torch.from_numpy(cells).cuda(), torch.from_numpy(lum).cuda()))
+        ref = plan.field(0, 0)
+        out = [torch.empty((n,) * 3, device="cuda")]
+        plan.step(dev, out)
+        assert torch.isfinite(ref).all() and ref.abs().max() > 0
+        assert torch.equal(ref, out[0])
+    plan.close()
